@@ -91,192 +91,287 @@ __device__ bool attempt_pair(const LigDev& L, int a, int b, int sep,
 
 // The all-separations sweep with the state data staged in LDS.  Within one
 // separation d, pair (a, a + d) only touches states of residue a mod d, so
-// the d residue classes are independent chains, each taken in ascending a.
-// A chain is a sequence of runs: the replica of the run's first state q is
-// carried up the chain while its swaps are accepted and stays at the state
-// where one is rejected (or where the chain ends); the next run starts one
-// step further up with that state's own replica.  When pair (a, a + d) is
-// attempted, state a + d still holds its replica from the start of the
-// pass, so the run that starts at q depends only on q and the labels at
-// the start of the pass.  Every possible run is therefore followed at once,
-// one thread per first state; then one thread per class walks the runs that
-// actually happen (first state of the class, then one state past each
-// run's end) and every state takes its new replica.  The energies are the
-// same double sums as state_energy and each attempt sees the replicas the
+// the d residue classes are independent chains, each taken in ascending a by
+// a wavefront of its own (position t of class rho = state rho + t d, one per
+// lane, in blocks of 64).  A chain is a sequence of runs: the replica of the
+// run's first position q is carried up the chain while its swaps are accepted
+// and stays at the position where one is rejected (or where the chain ends);
+// the next run starts one position further up with that position's own
+// replica.  When pair (t, t + 1) is attempted, position t + 1 still holds its
+// replica from the start of the pass, so whether the replica of q would pass
+// from t to t + 1 depends only on (q, t) and the labels at the start of the
+// pass: the attempts of a run are independent of each other.
+//   1. every state's energy with its own replica and with the next one's, and
+//      its own replica's at the kXAhead states above it (two threads a state);
+//   2. with those, the first kXAhead steps of the run that would start at
+//      each state, all at once;
+//   3. the class's wavefront walks the runs that happen (scalar, one lane
+//      read per run); a run still open after those steps is finished by one
+//      attempt per lane, the replica's at every later position of the block,
+//      and the first rejection found by a ballot; then a bit per run start
+//      gives every position its new replica.
+// The cost is latency: three barriers and about twenty dependent LDS round
+// trips a pass (1.1k + 0.8k cycles for steps 1 and 2; 2k for step 3 where a
+// class fits one block, 4-7k over two or three), not the longest run's
+// length in steps, as when one lane per first position follows its run step
+// by step (170 states, 25 sweeps of 5 separations, neighbours swapping at
+// 0.87: 926 us a call so, 334 us this way).  kXAhead: 4, 6 and 8 steps give
+// 372, 355 and 354 us; with the walk's doublings as well, 334.  The energies are the same
+// double sums as state_energy and each attempt sees the replicas the
 // one-thread order gives it, so every decision is that order's.
 constexpr int kXStates = 256, kXChannels = 5;
-struct XStage {
+constexpr int kXAhead = 8;      // steps decided ahead of the walk
+constexpr int kXHalf = kXAhead / 2;
+constexpr int kXJump = 3;       // doublings of the walk's step
+constexpr int kXThreads = 512;  // block of the exchange kernels
+struct alignas(16) XStage {
   double cp[kXStates * (1 + kXChannels)];  // components per replica
-  double wd[kXStates * kXChannels];        // weights per state
-  double beta[kXStates];
-  double ecur[2][kXStates];  // energy of the replica in state k at state k
-  double lnu[2][kXStates];   // ln u of a pass, by lower state (two buffers)
-  double eo[kXStates];       // energy of the replica in a + d at state a
-  double erest[kXStates];    // run from q: energy of its replica where it stays
-  int ros[2][kXStates];      // replica of each state (two buffers)
-  int rest[kXStates];        // run from q: the state where its replica stays
-  int owner[kXStates];       // first state of the run that ends at k, or -1
-  int ntry[kXStates], nacc[kXStates];  // separation-1 counts, by lower state
+  double sw[kXStates * (1 + kXChannels)];  // weights and beta per state
+  // by lower state of a pair: energy of the replica in a + d at state a, and
+  // ln u of the pass (two buffers, by pass)
+  double2 el[2][kXStates];
+  double ecur[kXStates];  // energy of the replica in state k at state k
+  int ros[2][kXStates];   // replica of each state (two buffers)
+  int len[2][kXStates];   // swaps ahead of a run from the state, by halves
+  int nacc[kXStates];     // accepted swaps of separation 1, by lower state
 };
 
-// state-k energy of components v, in the order of state_energy
+// 1 + C doubles of a staged array's entry, as 16-byte reads
+template <int C>
+__device__ __forceinline__ void staged_load(const double* p,
+                                            double (&v)[1 + C]) {
+  static_assert((1 + C) % 2 == 0, "entries are read as double2");
+  const double2* q = reinterpret_cast<const double2*>(p);
+#pragma unroll
+  for (int e = 0; e < (1 + C) / 2; ++e) {
+    const double2 t = q[e];
+    v[2 * e] = t.x;
+    v[2 * e + 1] = t.y;
+  }
+}
+// energy of components v at a state of weights u (u[C]: its beta), in the
+// order of state_energy
 template <int C>
 __device__ __forceinline__ double staged_sum(const double (&v)[1 + C],
-                                             const double (&u)[C]) {
+                                             const double (&u)[1 + C]) {
   double E = v[0];
 #pragma unroll
   for (int c = 0; c < C; ++c) E += u[c] * v[1 + c];
   return E;
 }
-template <int C>
-__device__ __forceinline__ double staged_energy(const XStage& X, int k,
-                                                int r) {
-  double v[1 + C], u[C];
-#pragma unroll
-  for (int e = 0; e <= C; ++e) v[e] = X.cp[r * (1 + C) + e];
-#pragma unroll
-  for (int c = 0; c < C; ++c) u[c] = X.wd[k * C + c];
-  return staged_sum<C>(v, u);
-}
 
 // ladders of up to kXTable states also keep the whole table E(k, r) of
-// every replica's energy at every state, computed once per call: a run
-// step then reads one entry instead of summing components
+// every replica's energy at every state, computed once per call: an attempt
+// then reads its energies instead of summing components
 constexpr int kXTable = 64;
 
+// the Metropolis test of attempt_pair
+__device__ __forceinline__ bool staged_accepts(double ba, double bb,
+                                               double2 el, double e,
+                                               double eba, double ebb) {
+  const double delta = ba * (el.x - e) + bb * (eba - ebb);
+  return (bool)(isfinite(delta) & (el.y < -delta));
+}
+
+constexpr unsigned kXOpen = 1u << 16;  // mark of an open run in the walk
+
+// Step 3 for one class by one wavefront: X.ros[cur] read, the other buffer
+// written.  count: add the accepted swaps of every pair to X.nacc.
 template <int C, bool TABLE>
-__device__ void exchange_all_staged(const LigDev& L, uint64_t sweep,
-                                    int max_sep, int n_sub, uint64_t seed,
-                                    XStage& X, double* em) {
-  const int K = L.K, C1 = 1 + C;
+__device__ __forceinline__ void exchange_class(XStage& X, const double* em,
+                                               int K, int d, int rho, int cur,
+                                               int lb, bool count) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int T = (K - rho + d - 1) / d;  // positions of the class
+  const int* ros = X.ros[cur];
+  const double2* el = X.el[lb];
+  // the lane's operands of block `held` (positions past the last pair: unused)
+  int held = -1;
+  double hw0[1 + C], hw1[1 + C], hec = 0.0;
+  double2 hel = make_double2(0.0, 0.0);
+  int q = 0, before = 0;  // next run's start, last start below the block
+  for (int b0 = 0; b0 < T; b0 += kWave) {
+    const int t = b0 + lane, ac = rho + (t < T ? t : T - 1) * d;
+    const int rep = ros[ac];
+    int ln = X.len[0][ac];
+    if (ln == kXHalf) ln += X.len[1][ac];
+    // the next run's start, relative to the block, or an open run's position
+    // (a pair above it is left to attempt) with a mark
+    unsigned next =
+        ln == kXAhead && t + kXAhead < T - 1
+            ? (unsigned)(t + kXAhead) | kXOpen : (unsigned)(lane + ln + 1);
+    const unsigned lim = T - b0 < kWave ? T - b0 : kWave;
+    // up to 2^kXJump runs in a row as one: the starts met and what follows
+    unsigned mlo = lane < 32 ? 1u << lane : 0u;
+    unsigned mhi = lane < 32 ? 0u : 1u << (lane - 32);
+#pragma unroll
+    for (int i = 0; i < kXJump; ++i) {
+      const int src = 4 * (int)(next < lim ? next : (unsigned)lane);
+      mlo |= (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)mlo);
+      mhi |= (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)mhi);
+      next = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)next);
+    }
+    unsigned long long start = 0ull;
+    unsigned qr = q - b0;
+    while (qr < lim) {
+      do {
+        const unsigned lo = __builtin_amdgcn_readlane(mlo, qr);
+        const unsigned hi = __builtin_amdgcn_readlane(mhi, qr);
+        start |= (unsigned long long)hi << 32 | lo;
+        qr = __builtin_amdgcn_readlane(next, qr);
+      } while (qr < lim);
+      if (qr & kXOpen) {
+        // the open run is the last one met
+        const int rq = __builtin_amdgcn_readlane(
+            rep, 63 - __builtin_clzll(start));
+        double cv[1 + C];
+        if (!TABLE) staged_load<C>(X.cp + rq * (1 + C), cv);
+        // attempts of the carried replica at positions p, p + 1, ...
+        for (int p = qr & (kXOpen - 1);;) {
+          const int blk = (unsigned)p / kWave;
+          const int ta = kWave * blk + lane;
+          const bool live = ta >= p && ta + 1 < T;
+          const int s0 = rho + (ta + 1 < T ? ta : T - 2) * d, s1 = s0 + d;
+          if (blk != held) {
+            held = blk;
+            hel = el[s0];
+            hec = X.ecur[s1];
+            staged_load<C>(X.sw + s0 * (1 + C), hw0);
+            staged_load<C>(X.sw + s1 * (1 + C), hw1);
+          }
+          const double e0 =
+              TABLE ? em[s0 * kXTable + rq] : staged_sum<C>(cv, hw0);
+          const double e1 =
+              TABLE ? em[s1 * kXTable + rq] : staged_sum<C>(cv, hw1);
+          const bool ok = staged_accepts(hw0[C], hw1[C], hel, e0, e1, hec);
+          const unsigned long long no = __ballot(live && !ok);
+          if (no) {
+            qr = kWave * blk + __builtin_ctzll(no) + 1 - b0;
+            break;
+          }
+          p = kWave * (blk + 1);
+          if (p >= T - 1) {
+            qr = T - b0;
+            break;
+          }
+        }
+      }
+    }
+    q = b0 + qr;
+    // a position where a run ends takes the run's replica; any other one had
+    // its swap with the position above accepted
+    const unsigned long long at = start & (~0ull >> (63 - lane));
+    const int qs = at ? b0 + 63 - __builtin_clzll(at) : before;
+    const unsigned long long up =
+        (start >> 1) | (q == b0 + kWave ? 1ull << 63 : 0ull);
+    if (t < T) {
+      const int a = rho + t * d;
+      const bool ends = t == T - 1 || ((up >> lane) & 1ull);
+      X.ros[cur ^ 1][a] = ros[ends ? rho + qs * d : a + d];
+      if (count && !ends) X.nacc[a] += 1;
+    }
+    if (start) before = b0 + 63 - __builtin_clzll(start);
+  }
+}
+
+template <int C, bool TABLE>
+__device__ __forceinline__ void exchange_all_staged(
+    const LigDev& L, uint64_t sweep, int max_sep, int n_sub, uint64_t seed,
+    XStage& X, double* em) {
+  constexpr int C1 = 1 + C;
+  const int K = L.K;
   const int tid = threadIdx.x, nt = blockDim.x;
-  for (int i = tid; i < K * C1; i += nt) X.cp[i] = L.comps[i];
-  for (int i = tid; i < K * C; i += nt) X.wd[i] = L.wd[i];
+  const int nw = nt / kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int i = tid; i < K * C1; i += nt) {
+    const int k = i / C1, c = i - k * C1;
+    X.cp[i] = L.comps[i];
+    X.sw[i] = c < C ? L.wd[k * C + c] : L.beta[k];
+  }
   for (int k = tid; k < K; k += nt) {
-    X.beta[k] = L.beta[k];
     X.ros[0][k] = L.replica_of_state[k];
-    X.ntry[k] = 0;
     X.nacc[k] = 0;
   }
   __syncthreads();
-  for (int k = tid; k < K; k += nt)
-    X.ecur[0][k] = staged_energy<C>(X, k, X.ros[0][k]);
-  if (TABLE)
-    for (int q = tid; q < K * K; q += nt)
-      em[(q / K) * kXTable + q % K] = staged_energy<C>(X, q / K, q % K);
-  __syncthreads();
+  if (TABLE) {
+    for (int i = tid; i < K * K; i += nt) {
+      const int k = i / K, r = i - k * K;
+      double v[C1], u[C1];
+      staged_load<C>(X.cp + r * C1, v);
+      staged_load<C>(X.sw + k * C1, u);
+      em[k * kXTable + r] = staged_sum<C>(v, u);
+    }
+  }
   int cur = 0, lb = 0;
   const int dmax = max_sep < K - 1 ? max_sep : K - 1;
   // ln u of the pass (j, d) into buffer b, by threads t0, t0 + stride, ...
   auto draw_pass = [&](int j, int d, int b, int t0, int stride) {
     const uint32_t purpose = (uint32_t)kExchange | ((uint32_t)d << 8);
     for (int a = t0; a + d < K; a += stride)
-      X.lnu[b][a] =
+      X.el[b][a].y =
           log(u01d(draw(seed, (uint32_t)a, L.id, j, sweep, purpose).x));
   };
   if (n_sub > 0 && dmax > 0) draw_pass(0, 1, 0, tid, nt);
+  if (TABLE) __syncthreads();
+  // steps 1 and 2: threads 0..255 and 256..511 (half h) each take the state
+  // tid mod 256, whose weights they keep in registers
+  static_assert(kXThreads == 2 * kXStates, "two threads a state");
+  const int h = tid / kXStates, a = tid - h * kXStates;
+  const bool act = a < K;
+  double ua[C1];
+  staged_load<C>(X.sw + (act ? a : 0) * C1, ua);
   for (int j = 0; j < n_sub; ++j) {
     for (int d = 1; d <= dmax; ++d) {
       const int* ros = X.ros[cur];
-      const double* ecur = X.ecur[cur];
-      const double* lnu = X.lnu[lb];
-      // the upper replica's energy at the lower state
-      for (int a = tid; a < K; a += nt) {
-        X.owner[a] = -1;
-        if (a + d < K)
-          X.eo[a] = TABLE ? em[a * kXTable + ros[a + d]]
-                          : staged_energy<C>(X, a, ros[a + d]);
-      }
-      __syncthreads();
-      // the run that starts at q, for every q; each step's operands are
-      // loaded while the step before it is decided
-      for (int q = tid; q < K; q += nt) {
-        int a = q;
-        double e = ecur[q];  // energy of the carried replica at state a
-        if (q + d < K) {
-          const int r = ros[q];
-          double v[1 + C], wb[C], et = 0.0;
-          if (!TABLE)
-#pragma unroll
-            for (int i = 0; i <= C; ++i) v[i] = X.cp[r * C1 + i];
-          int b = a + d;
-          double ba = X.beta[a], eoa = X.eo[a], lna = lnu[a];
-          double bb = X.beta[b], ebb = ecur[b];
-          if (TABLE)
-            et = em[b * kXTable + r];
-          else
-#pragma unroll
-            for (int c = 0; c < C; ++c) wb[c] = X.wd[b * C + c];
-          for (;;) {
-            // the next step's operands (unused when this step ends the run)
-            const int b2 = b + d < K ? b + d : b;
-            const double neo = X.eo[b], nln = lnu[b];
-            const double nbb = X.beta[b2], neb = ecur[b2];
-            double nwb[C], net = 0.0;
-            if (TABLE)
-              net = em[b2 * kXTable + r];
-            else
-#pragma unroll
-              for (int c = 0; c < C; ++c) nwb[c] = X.wd[b2 * C + c];
-            // the carried replica at state b
-            const double eba = TABLE ? et : staged_sum<C>(v, wb);
-            const double delta = ba * (eoa - e) + bb * (eba - ebb);
-            const bool ok = isfinite(delta) && (lna < -delta);
-            if (!ok) break;
-            e = eba;
-            a = b;
-            if (a + d >= K) break;
-            b = b2;
-            ba = bb;
-            eoa = neo;
-            lna = nln;
-            bb = nbb;
-            ebb = neb;
-            et = net;
-#pragma unroll
-            for (int c = 0; c < C; ++c) wb[c] = nwb[c];
-          }
+      double2* el = X.el[lb];
+      // energies of the state's replica at the half's states, the energy at
+      // the state of its own (h = 0) or the next state's replica (h = 1)
+      double e[kXHalf + 1], be[kXHalf + 1];
+      int st[kXHalf + 1];
+      if (act) {
+        const int r = ros[a], r1 = ros[a + d < K ? a + d : a];
+        double v[C1], v1[C1];
+        if (!TABLE) {
+          staged_load<C>(X.cp + r * C1, v);
+          if (h == 1) staged_load<C>(X.cp + r1 * C1, v1);
         }
-        X.rest[q] = a;
-        X.erest[q] = e;
-      }
-      __syncthreads();
-      // the next pass's uniforms, by the threads past the first wavefront
-      // while it walks (by every thread, before its walk, in a block of
-      // one wavefront)
-      {
-        const int dn = d < dmax ? d + 1 : 1, jn = d < dmax ? j : j + 1;
-        const int t0 = nt > kWave ? kWave : 0;
-        if (jn < n_sub && tid >= t0)
-          draw_pass(jn, dn, lb ^ 1, tid - t0, nt - t0);
-      }
-      // the runs that happen: from the class's first state, each one
-      // starting one step past the previous one's end
-      for (int rho = tid; rho < d; rho += nt)
-        for (int q = rho; q < K;) {
-          const int a = X.rest[q];
-          X.owner[a] = q;
-          q = a + d;
+#pragma unroll
+        for (int m = 0; m <= kXHalf; ++m) {
+          const int s = a + (kXHalf * h + m) * d;
+          st[m] = s < K ? s : a;  // past the end: any state (not counted)
+          double u[C1];
+          staged_load<C>(X.sw + st[m] * C1, u);
+          e[m] = TABLE ? em[st[m] * kXTable + r] : staged_sum<C>(v, u);
+          be[m] = u[C];
         }
-      __syncthreads();
-      // a state where a run ends takes the run's replica; any other state
-      // had its swap with the state d above accepted
-      int* nros = X.ros[cur ^ 1];
-      double* necur = X.ecur[cur ^ 1];
-      for (int a = tid; a < K; a += nt) {
-        const int q = X.owner[a];
-        if (q >= 0) {
-          nros[a] = ros[q];
-          necur[a] = X.erest[q];
+        if (h == 0) {
+          X.ecur[a] = e[0];
         } else {
-          nros[a] = ros[a + d];
-          necur[a] = X.eo[a];
-        }
-        if (d == 1 && a + 1 < K) {
-          X.ntry[a] += 1;
-          X.nacc[a] += (int)(q < 0);
+          el[a].x = TABLE ? em[a * kXTable + r1] : staged_sum<C>(v1, ua);
         }
       }
+      __syncthreads();
+      if (act) {
+        int len = 0;
+        bool go = true;
+#pragma unroll
+        for (int m = 0; m < kXHalf; ++m) {
+          const bool ok = staged_accepts(be[m], be[m + 1], el[st[m]], e[m],
+                                         e[m + 1], X.ecur[st[m + 1]]);
+          go = (bool)(go & ok & (a + (kXHalf * h + m + 1) * d < K));
+          len += go ? 1 : 0;
+        }
+        X.len[h][a] = len;
+      }
+      __syncthreads();
+      // (3) the walk; the next pass's uniforms by the wavefronts without a
+      // class meanwhile (by every one, first, when all have classes)
+      const int dn = d < dmax ? d + 1 : 1, jn = d < dmax ? j : j + 1;
+      const int w0 = d < nw ? d : 0;
+      if (jn < n_sub && wv >= w0)
+        draw_pass(jn, dn, lb ^ 1, tid - w0 * kWave, nt - w0 * kWave);
+      for (int rho = wv; rho < d; rho += nw)
+        exchange_class<C, TABLE>(X, em, K, d, rho, cur, lb, d == 1);
       cur ^= 1;
       lb ^= 1;
       __syncthreads();
@@ -286,8 +381,8 @@ __device__ void exchange_all_staged(const LigDev& L, uint64_t sweep,
     const int r = X.ros[cur][k];
     L.replica_of_state[k] = r;
     L.state_of_replica[r] = k;
-    if (k + 1 < K && X.ntry[k]) {
-      atomicAdd(&L.ex_try[k], (unsigned long long)X.ntry[k]);
+    if (k + 1 < K && dmax > 0) {
+      atomicAdd(&L.ex_try[k], (unsigned long long)n_sub);
       if (X.nacc[k]) atomicAdd(&L.ex_acc[k], (unsigned long long)X.nacc[k]);
     }
   }
@@ -296,8 +391,11 @@ __device__ void exchange_all_staged(const LigDev& L, uint64_t sweep,
 
 // block-wide exchange for one ligand (called by all threads): n_sub
 // exchange sweeps in a row, sweep j drawing its uniforms with replica field j
-__device__ void exchange_block(const LigDev& L, uint64_t sweep, int scheme,
-                               int max_sep, int n_sub, uint64_t seed) {
+// Inlined into its kernels, with everything below it: in a called function
+// the staged data's pointers are generic and every access a flat one.
+__device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
+                                               int scheme, int max_sep,
+                                               int n_sub, uint64_t seed) {
   __shared__ XStage X;
   __shared__ double em[kXTable * kXTable];
   const int K = L.K;
@@ -333,9 +431,9 @@ __device__ void exchange_block(const LigDev& L, uint64_t sweep, int scheme,
 
 // Tail of one ligand's sweep, run by one whole block: exchange (if due),
 // record one sample per state (if due), counter += 1.
-__device__ void sweep_tail(const LigDev& L, int exchange_every, int scheme,
-                           int max_sep, int n_sub, int sample_every,
-                           uint64_t seed) {
+__device__ __forceinline__ void sweep_tail(const LigDev& L, int exchange_every,
+                                           int scheme, int max_sep, int n_sub,
+                                           int sample_every, uint64_t seed) {
   const unsigned long long s = *L.counter;
   if (exchange_every > 0 && s % (unsigned long long)exchange_every == 0ull)
     exchange_block(L, s, scheme, max_sep, n_sub, seed);
@@ -365,7 +463,7 @@ __device__ void sweep_tail(const LigDev& L, int exchange_every, int scheme,
 }
 
 // One block per ligand: the tail as a kernel of its own.
-__global__ __launch_bounds__(256) void k_sweep_tail(
+__global__ __launch_bounds__(kXThreads) void k_sweep_tail(
     const LigDev* __restrict__ ligs, int exchange_every, int scheme,
     int max_sep, int n_sub, int sample_every, uint64_t seed) {
   sweep_tail(ligs[blockIdx.x], exchange_every, scheme, max_sep, n_sub,
@@ -694,7 +792,7 @@ __global__ __launch_bounds__(W * kWave) void k_hmc_sweep(
   }
 }
 
-__global__ __launch_bounds__(256) void k_exchange(
+__global__ __launch_bounds__(kXThreads) void k_exchange(
     const LigDev* __restrict__ ligs, int scheme, int max_sep, int n_sub,
     uint64_t seed) {
   const LigDev& L = ligs[blockIdx.x];
@@ -1221,7 +1319,7 @@ hipError_t launch_sweep_tail(const LigDev* d_ligs, int n_ligs,
                              int n_sub, int sample_every, uint64_t seed,
                              hipStream_t st) {
   if (n_ligs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sweep_tail, dim3(n_ligs), dim3(256), 0, st, d_ligs,
+  hipLaunchKernelGGL(k_sweep_tail, dim3(n_ligs), dim3(kXThreads), 0, st, d_ligs,
                      exchange_every, scheme, max_sep, n_sub, sample_every,
                      seed);
   return hipGetLastError();
@@ -1247,7 +1345,7 @@ hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
                            int max_sep, int n_sub, uint64_t seed,
                            hipStream_t st) {
   if (n_ligs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_exchange, dim3(n_ligs), dim3(256), 0, st, d_lig,
+  hipLaunchKernelGGL(k_exchange, dim3(n_ligs), dim3(kXThreads), 0, st, d_lig,
                      scheme, max_sep, n_sub, seed);
   return hipGetLastError();
 }

@@ -216,6 +216,42 @@ def test_exchange_runs_edge_cases(K, C, mode):
         assert stats["ex_acc"].sum() > 0.9 * n_try
     ctx.close()
 
+
+@pytest.mark.parametrize("K,C,max_sep", [
+    (2, 3, 5), (3, 5, 5), (9, 3, 9), (10, 5, 20), (63, 5, 5), (64, 3, 12),
+    (65, 5, 5), (66, 3, 1), (127, 3, 2), (128, 5, 5), (129, 5, 9),
+    (193, 3, 7), (255, 5, 3), (256, 5, 300)])
+@pytest.mark.parametrize("scale", [0.05, 0.6, 6.0])
+def test_exchange_walk_block_edges(K, C, max_sep, scale):
+    """All-separation sweeps where the walk's blocks of 64 positions, its
+    steps decided ahead and its wavefronts run out: chains one position
+    short of, at and past a block, separations past the block's wavefronts
+    and past the ladder, run lengths from one swap to several blocks.
+    Labels and counts equal the oracle's."""
+    print_case("exchange walk", K, C, max_sep, scale)
+    g, lig = _exchange_ligand(K, C)
+    rng = np.random.default_rng([K, C, int(10 * scale)])
+    comps = rng.normal(scale=scale, size=(K, 1 + C))
+    sor = rng.permutation(K).astype(np.int32)
+    ctx, (lid,) = make_context(g, [lig], seed=29)
+    ctx.set_replicas(lid, lig.x0, sor, comps, 8)
+    n_sweeps = 2 if max_sep > 12 else 6
+    ctx.exchange(lid, scheme=1, max_sep=max_sep, n_sweeps=n_sweeps)
+    st = ctx.get_replicas(lid)
+    s = oracle.Sampler(oracle.OGrid(g), oracle.OLigand(lig), seed=29,
+                       lig_id=lid, x0=lig.x0)
+    s.comps = np.ascontiguousarray(comps)
+    s.state = sor.copy()
+    s.rep_of_state = np.ascontiguousarray(np.argsort(sor).astype(np.int32))
+    s.sweep_count = 8
+    s.exchange(scheme=1, max_sep=max_sep, n_sweeps=n_sweeps)
+    assert np.array_equal(st["state_of_replica"], s.state)
+    stats = ctx.get_stats(lid)
+    assert np.array_equal(stats["ex_try"], s.ex_try)
+    assert np.array_equal(stats["ex_acc"], s.ex_acc)
+    ctx.close()
+
+
 def test_checkpoint_resume_is_bitwise():
     print_case("checkpoint")
     system = synth.make_system(1)
