@@ -327,11 +327,12 @@ BPMF_API int bpmf_mbar(bpmf_ctx* ctx, const double* dev_ukn, int K, int64_t N,
  * sum of K entries; var may be NULL), n_iter n_problems ints (may be NULL).
  * Each problem gets exactly the iteration, stopping rule and result
  * bpmf_mbar gives it alone (bpmf_mbar is this call with one problem); the
- * batch advances every unfinished problem by one step per round, so the
- * host waits for the device about three times per iteration of the slowest
- * problem, not per problem.  Scratch grows with the sum over problems of
- * N + 8 (K + K^2) x (N / (4096 / Kp)) doubles (Kp = K rounded up to 16, 32,
- * 64 or 128).  Errors: BPMF_E_INVAL naming the offending problem (nothing is
+ * batch advances every unfinished problem by one step per round; the steps'
+ * decisions are the device's, and the host enqueues a few rounds ahead until
+ * the last problem is done.  Scratch grows with the sum over problems of
+ * N + min(256, N / 128 or N / 64) x (16 (t + 1) + 128 t (t + 1)) doubles
+ * (t = K / 16, rounded up; both quotients rounded up, N / 64 from 49 states
+ * on).  Errors: BPMF_E_INVAL naming the offending problem (nothing is
  * computed). */
 BPMF_API int bpmf_mbar_batch(bpmf_ctx* ctx, int n_problems,
                              const double* const* dev_ukn, const int* K,

@@ -129,6 +129,9 @@ struct bpmf_ctx {
   hipEvent_t jobs_copied = nullptr;  // last upload of the staging buffer
   void* mbar_mem = nullptr;
   size_t mbar_bytes = 0;
+  int* mbar_flag = nullptr;  // pinned: set when a solve's last problem is done
+  static constexpr int kMbarAhead = 3;  // rounds enqueued ahead of the device
+  hipEvent_t mbar_round[kMbarAhead] = {};
   void* mlp_mem = nullptr;   // activations of the proposal network
   size_t mlp_bytes = 0;
   void* place_mem = nullptr;  // centres of mass of placed configurations
@@ -432,6 +435,9 @@ extern "C" int bpmf_destroy(bpmf_ctx* c) {
   if (c->jobs_host) (void)hipHostFree(c->jobs_host);
   if (c->jobs_copied) (void)hipEventDestroy(c->jobs_copied);
   c->dfree(c->mbar_mem);
+  if (c->mbar_flag) (void)hipHostFree(c->mbar_flag);
+  for (hipEvent_t e : c->mbar_round)
+    if (e) (void)hipEventDestroy(e);
   for (int k = 0; k < bpmf_ctx::kTimers; ++k)
     for (hipEvent_t e : c->ev_pool[k]) (void)hipEventDestroy(e);
   c->drop_graph();
@@ -1571,22 +1577,11 @@ extern "C" int bpmf_energy_matrix(bpmf_ctx* c, int ligand_id,
                                   &dev_ukn, &ld);
 }
 
-namespace {
-// host side of one problem of an MBAR batch
-struct MbarSolve {
-  enum Phase { kNewtonStep, kSearch, kFixedPoint, kDone };
-  Phase phase = kNewtonStep;
-  int it = 1;         // current iteration (1-based)
-  int ls = 0;         // line-search trials made in this iteration
-  bool accept = false;  // ftry becomes f at the start of the next round
-  double trust = INFINITY, Fcur = 0.0, t = 1.0, maxstep = 0.0, gs = 0.0;
-  int n_iter = 0;
-};
-}  // namespace
-
 // Solves every problem of the batch with the same sequence of steps a lone
-// solve takes, advancing all unfinished problems by one step per round (one
-// host synchronisation per round for the whole batch).  Per problem and
+// solve takes, advancing all unfinished problems by one step per round.  The
+// decisions are the device's (MbarState), so the host only enqueues rounds,
+// a few ahead of the device, until the last problem has set the context's
+// host flag; rounds enqueued past that do nothing.  Per problem and
 // iteration: a Newton step with backtracking on the objective when the
 // gauge-fixed Hessian is numerically positive definite, otherwise one
 // fixed-point step (far from the solution whole states' weights can
@@ -1650,70 +1645,76 @@ extern "C" int bpmf_mbar_batch(bpmf_ctx* c, int n_problems,
   }
   if (act.empty()) return BPMF_OK;
   const int64_t sumK = koff[P];
-  int max_K = 0, max_nb = 0, max_acc[9] = {0};
-  size_t n_logD = 0, n_obj = 0, n_part = 0, n_red = 0, n_mat = 0;
+  constexpr int kMaxTiles = (BPMF_MAX_MBAR_STATES + 15) / 16;
+  static_assert(kMaxTiles % 2 == 0, "steps take tile counts in pairs");
+  int max_K = 0;
+  int max_nb[kMaxTiles + 1] = {0};
+  size_t n_logD = 0, n_part = 0, n_red = 0;
   for (int p : act) {
-    const int K = Ks[p];
-    const int ts = mbar_acc_ts(K);
+    const int K = Ks[p], nt = mbar_tiles(K);
     max_K = std::max(max_K, K);
-    max_nb = std::max(max_nb, mbar_logD_blocks(Ns[p]));
-    max_acc[ts] = std::max(max_acc[ts], mbar_acc_blocks(K, Ns[p]));
+    max_nb[nt] = std::max(max_nb[nt], mbar_blocks(K, Ns[p]));
     n_logD += Ns[p];
-    n_obj += mbar_logD_blocks(Ns[p]);
-    n_part += (size_t)mbar_acc_blocks(K, Ns[p]) * (K + (size_t)K * K);
-    n_red += K + (size_t)K * K;
-    n_mat += (size_t)(K - 1) * (2 * K - 1);
+    n_part += (size_t)mbar_blocks(K, Ns[p]) * mbar_width(K);
+    n_red += mbar_width(K);
   }
+  // the problems by tile count; the uploaded part of the scratch first: their
+  // table (which holds their states), the K-vectors and the done count
+  std::stable_sort(act.begin(), act.end(), [&](int p, int q) {
+    return mbar_tiles(Ks[p]) < mbar_tiles(Ks[q]);
+  });
+  const int n = (int)act.size();
+  int n_tile[kMaxTiles + 1] = {0};
+  for (int p : act) ++n_tile[mbar_tiles(Ks[p])];
   Arena A;
-  const size_t o_tab = A.add(P * sizeof(MbarProb)),
-               o_vec = A.add((size_t)6 * sumK * 8),
-               o_sc = A.add((size_t)P * 8 * 8), o_logD = A.add(n_logD * 8),
-               o_obj = A.add(n_obj * 8), o_part = A.add(n_part * 8),
-               o_red = A.add(n_red * 8), o_mat = A.add(n_mat * 8),
-               o_list = A.add((size_t)P * 4 * sizeof(int)),
-               o_t = A.add((size_t)P * 8);
+  const size_t o_tab = A.add(n * sizeof(MbarProb)), o_f = A.add(sumK * 8),
+               o_logN = A.add(sumK * 8), o_Nk = A.add(sumK * 8),
+               o_done = A.add(sizeof(int)), up_bytes = A.total,
+               // results: f, variances, iteration counts
+               o_res = A.add((2 * sumK + P) * 8), o_try = A.add(sumK * 8),
+               o_step = A.add(sumK * 8), o_logD = A.add(n_logD * 8),
+               o_part = A.add(n_part * 8),
+               o_red = A.add(n_red * 8);
   rc = ensure_scratch(c, &c->mbar_mem, &c->mbar_bytes, A.total);
   if (rc) return rc;
+  if (!c->mbar_flag)
+    HIP_TRY(hipHostMalloc((void**)&c->mbar_flag, sizeof(int)));
+  for (hipEvent_t& e : c->mbar_round)
+    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   char* base = (char*)c->mbar_mem;
-  double* vec = (double*)(base + o_vec);
-  double *d_f = vec, *d_ftry = vec + sumK, *d_logN = vec + 2 * sumK,
-         *d_Nk = vec + 3 * sumK, *d_step = vec + 4 * sumK,
-         *d_var = vec + 5 * sumK;
-  double* d_sc = (double*)(base + o_sc);
-  const MbarProb* d_tab = (const MbarProb*)(base + o_tab);
-  int* d_list = (int*)(base + o_list);
-  double* d_t = (double*)(base + o_t);
-  std::vector<MbarProb> tab(P);
-  std::vector<double> h_logN(sumK, 0.0), h_Nk(sumK, 1.0), h_f(sumK, 0.0);
+  std::vector<char> up(up_bytes, 0);
+  MbarProb* tab = (MbarProb*)(up.data() + o_tab);
+  double *h_f = (double*)(up.data() + o_f),
+         *h_logN = (double*)(up.data() + o_logN),
+         *h_Nk = (double*)(up.data() + o_Nk);
+  double* d_res = (double*)(base + o_res);
   {
-    size_t qd = 0, qo = 0, qp = 0, qr = 0, qm = 0;
-    for (int p : act) {
-      const int K = Ks[p];
-      MbarProb& q = tab[p];
+    size_t qd = 0, qp = 0, qr = 0;
+    for (int j = 0; j < n; ++j) {
+      const int p = act[j], K = Ks[p];
+      MbarProb& q = tab[j];
       q.ukn = dev_ukn[p];
       q.N = Ns[p];
       q.ld = lds[p];
       q.K = K;
-      q.nb = mbar_logD_blocks(Ns[p]);
-      q.nb_acc = mbar_acc_blocks(K, Ns[p]);
-      q.ts = mbar_acc_ts(K);
-      q.f = d_f + koff[p];
-      q.ftry = d_ftry + koff[p];
-      q.logN = d_logN + koff[p];
-      q.Nk = d_Nk + koff[p];
-      q.step = d_step + koff[p];
-      q.var = d_var + koff[p];
-      q.scalars = d_sc + (size_t)p * 8;
+      q.nb = mbar_blocks(K, Ns[p]);
+      q.f = d_res + koff[p];
+      q.var = d_res + sumK + koff[p];
+      q.iter = d_res + 2 * sumK + p;
+      q.ftry = (double*)(base + o_try) + koff[p];
+      q.step = (double*)(base + o_step) + koff[p];
+      q.logN = (double*)(base + o_logN) + koff[p];
+      q.Nk = (double*)(base + o_Nk) + koff[p];
       q.logD = (double*)(base + o_logD) + qd;
-      q.obj_part = (double*)(base + o_obj) + qo;
       q.partial = (double*)(base + o_part) + qp;
       q.red = (double*)(base + o_red) + qr;
-      q.mat = (double*)(base + o_mat) + qm;
       qd += Ns[p];
-      qo += q.nb;
-      qp += (size_t)q.nb_acc * (K + (size_t)K * K);
-      qr += K + (size_t)K * K;
-      qm += (size_t)(K - 1) * (2 * K - 1);
+      qp += (size_t)q.nb * mbar_width(K);
+      qr += mbar_width(K);
+      q.state.phase = kMbarStart;
+      q.state.it = 1;
+      q.state.trust = INFINITY;
+      q.state.t = 1.0;
       for (int k = 0; k < K; ++k) {
         h_Nk[koff[p] + k] = (double)N_k[koff[p] + k];
         h_logN[koff[p] + k] = log(h_Nk[koff[p] + k]);
@@ -1721,172 +1722,46 @@ extern "C" int bpmf_mbar_batch(bpmf_ctx* c, int n_problems,
       }
     }
   }
-  HIP_TRY(hipMemcpyAsync(base + o_tab, tab.data(), P * sizeof(MbarProb),
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(d_f, h_f.data(), sumK * 8, hipMemcpyHostToDevice,
+  *c->mbar_flag = 0;
+  HIP_TRY(hipMemcpyAsync(base, up.data(), up_bytes, hipMemcpyHostToDevice,
                          c->stream));
-  HIP_TRY(hipMemcpyAsync(d_logN, h_logN.data(), sumK * 8,
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(d_Nk, h_Nk.data(), sumK * 8, hipMemcpyHostToDevice,
+  HIP_TRY(hipMemcpyAsync(d_res, base + o_f, sumK * 8, hipMemcpyDeviceToDevice,
                          c->stream));
-  std::vector<MbarSolve> S(P);
-  std::vector<double> sc((size_t)P * 8);
-  // lists of one round, uploaded together: [accept | newton (by tile) |
-  // line search | fixed point]
-  std::vector<int> lists;
-  std::vector<double> tv(P, 0.0);
-  auto upload = [&]() -> int {
-    HIP_TRY(hipMemcpyAsync(d_list, lists.data(), lists.size() * sizeof(int),
-                           hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(d_t, tv.data(), P * 8, hipMemcpyHostToDevice,
-                           c->stream));
-    return BPMF_OK;
-  };
-  auto fetch = [&]() -> int {
-    HIP_TRY(hipMemcpyAsync(sc.data(), d_sc, (size_t)P * 64,
-                           hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return BPMF_OK;
-  };
-  // objective (and logD) at every starting point
-  lists = act;
-  if ((rc = upload())) return rc;
-  HIP_TRY(mbar_objective(d_tab, d_list, (int)act.size(), max_nb, 0,
-                         c->stream));
-  if ((rc = fetch())) return rc;
-  for (int p : act) S[p].Fcur = sc[(size_t)p * 8];
-  auto finish = [&](MbarSolve& s, double change) {
-    if (!(change >= tol)) {
-      s.phase = MbarSolve::kDone;
-      s.n_iter = s.it;
-    } else if (s.it >= max_iter) {
-      s.phase = MbarSolve::kDone;
-      s.n_iter = max_iter;
-    } else {
-      ++s.it;
-      s.phase = MbarSolve::kNewtonStep;
+  MbarProb* d_tab = (MbarProb*)(base + o_tab);
+  volatile int* flag = c->mbar_flag;
+  constexpr int kAhead = bpmf_ctx::kMbarAhead;
+  for (int64_t round = 0; *flag == 0; ++round) {
+    // at most kAhead rounds in flight
+    if (round >= kAhead)
+      HIP_TRY(hipEventSynchronize(c->mbar_round[round % kAhead]));
+    if (*flag != 0) break;
+    MbarProb* T = d_tab;
+    for (int nt = 1; nt <= kMaxTiles; ++nt) {
+      HIP_TRY(mbar_sums(T, n_tile[nt], nt, max_nb[nt], c->stream));
+      T += n_tile[nt];
     }
-  };
-  static const int kTiles[4] = {1, 2, 4, 8};
-  for (;;) {
-    lists.clear();
-    std::vector<int> newt, search, fixed;
-    for (int p : act)
-      if (S[p].accept) lists.push_back(p);
-    const int n_acc = (int)lists.size();
-    int n_tile[4] = {0, 0, 0, 0};
-    for (int i = 0; i < 4; ++i)
-      for (int p : act)
-        if (S[p].phase == MbarSolve::kNewtonStep && tab[p].ts == kTiles[i]) {
-          lists.push_back(p);
-          newt.push_back(p);
-          ++n_tile[i];
-        }
-    for (int p : act)
-      if (S[p].phase == MbarSolve::kSearch) {
-        lists.push_back(p);
-        search.push_back(p);
-        tv[p] = S[p].t;
-      }
-    for (int p : act)
-      if (S[p].phase == MbarSolve::kFixedPoint) {
-        lists.push_back(p);
-        fixed.push_back(p);
-      }
-    if (newt.empty() && search.empty() && fixed.empty()) break;
-    if ((rc = upload())) return rc;
-    const int* L = d_list;
-    HIP_TRY(mbar_accept(d_tab, L, n_acc, c->stream));
-    L += n_acc;
-    for (int p : act) S[p].accept = false;
-    const int* Ln = L;
-    for (int i = 0; i < 4; ++i) {
-      HIP_TRY(mbar_accumulate(d_tab, L, n_tile[i], kTiles[i],
-                              max_acc[kTiles[i]], c->stream));
-      L += n_tile[i];
+    HIP_TRY(mbar_reduce(d_tab, n, max_K, c->stream));
+    T = d_tab;
+    for (int nt = 2; nt <= kMaxTiles; nt += 2) {
+      const int cnt = n_tile[nt - 1] + n_tile[nt];
+      HIP_TRY(mbar_step(T, cnt, nt, tol, max_iter, (int*)(base + o_done), n,
+                        flag, c->stream));
+      T += cnt;
     }
-    HIP_TRY(mbar_newton(d_tab, Ln, (int)newt.size(), max_K, 0, c->stream));
-    HIP_TRY(mbar_axpy(d_tab, L, (int)search.size(), d_t, c->stream));
-    HIP_TRY(mbar_objective(d_tab, L, (int)search.size(), max_nb, 1,
-                           c->stream));
-    L += search.size();
-    HIP_TRY(mbar_fixed_point(d_tab, L, (int)fixed.size(), max_K, c->stream));
-    HIP_TRY(mbar_objective(d_tab, L, (int)fixed.size(), max_nb, 0,
-                           c->stream));
-    if ((rc = fetch())) return rc;
-    for (int p : newt) {
-      MbarSolve& s = S[p];
-      const double* q = &sc[(size_t)p * 8];
-      if (q[3] == 0.0) {
-        s.maxstep = q[1];
-        s.gs = q[2];
-        s.t = s.trust >= 1.0 ? std::min(1.0, 2.0 * s.trust / s.maxstep) : 1.0;
-        s.ls = 0;
-        s.phase = MbarSolve::kSearch;
-      } else {
-        s.phase = MbarSolve::kFixedPoint;
-      }
-    }
-    for (int p : search) {
-      MbarSolve& s = S[p];
-      const double Ftry = sc[(size_t)p * 8];
-      const bool ok = Ftry <= s.Fcur + 1e-4 * s.t * s.gs + 1e-13 * fabs(s.Fcur)
-                      || s.t * s.maxstep < tol;
-      if (!ok) {
-        s.t *= 0.5;
-        // after 60 trials the last one is taken anyway
-        if (++s.ls < 60) continue;
-      }
-      s.accept = true;
-      s.Fcur = Ftry;
-      const double change = s.t * s.maxstep;
-      s.trust = change;
-      finish(s, change);
-    }
-    for (int p : fixed) {
-      MbarSolve& s = S[p];
-      s.Fcur = sc[(size_t)p * 8];
-      finish(s, sc[(size_t)p * 8 + 4]);
-    }
+    HIP_TRY(mbar_self_consistent(d_tab, n, max_K, c->stream));
+    HIP_TRY(hipEventRecord(c->mbar_round[round % kAhead], c->stream));
   }
-  // variances at the solutions (logD recomputed at f)
-  lists.clear();
-  for (int p : act)
-    if (S[p].accept) lists.push_back(p);
-  const int n_acc = (int)lists.size();
-  int n_tile[4] = {0, 0, 0, 0};
-  for (int i = 0; i < 4; ++i)
-    for (int p : act)
-      if (tab[p].ts == kTiles[i]) {
-        lists.push_back(p);
-        ++n_tile[i];
-      }
-  if ((rc = upload())) return rc;
-  HIP_TRY(mbar_accept(d_tab, d_list, n_acc, c->stream));
-  const int* Ln = d_list + n_acc;
-  HIP_TRY(mbar_objective(d_tab, Ln, (int)act.size(), max_nb, 0, c->stream));
-  const int* L = Ln;
-  for (int i = 0; i < 4; ++i) {
-    HIP_TRY(mbar_accumulate(d_tab, L, n_tile[i], kTiles[i],
-                            max_acc[kTiles[i]], c->stream));
-    L += n_tile[i];
-  }
-  HIP_TRY(mbar_newton(d_tab, Ln, (int)act.size(), max_K, 1, c->stream));
-  std::vector<double> hf(sumK), hv(sumK);
-  HIP_TRY(hipMemcpyAsync(hf.data(), d_f, sumK * 8, hipMemcpyDeviceToHost,
-                         c->stream));
-  HIP_TRY(hipMemcpyAsync(hv.data(), d_var, sumK * 8, hipMemcpyDeviceToHost,
-                         c->stream));
-  if ((rc = fetch())) return rc;
+  // a Hessian that is not positive definite at the solution means states
+  // without overlap: their differences are not determined (variance +inf)
+  std::vector<double> res(2 * sumK + P);
+  HIP_TRY(hipMemcpyAsync(res.data(), d_res, res.size() * 8,
+                         hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(hipStreamSynchronize(c->stream));
   for (int p : act) {
     const int K = Ks[p];
-    memcpy(f + koff[p], hf.data() + koff[p], K * 8);
-    // a Hessian that is not positive definite at the solution means states
-    // without overlap: their differences are not determined
-    if (sc[(size_t)p * 8 + 3] != 0.0)
-      for (int k = 1; k < K; ++k) hv[koff[p] + k] = INFINITY;
-    if (var) memcpy(var + koff[p], hv.data() + koff[p], K * 8);
-    if (n_iter) n_iter[p] = S[p].n_iter;
+    memcpy(f + koff[p], res.data() + koff[p], K * 8);
+    if (var) memcpy(var + koff[p], res.data() + sumK + koff[p], K * 8);
+    if (n_iter) n_iter[p] = (int)res[2 * sumK + p];
   }
   return BPMF_OK;
 }

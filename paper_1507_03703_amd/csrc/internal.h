@@ -250,48 +250,65 @@ hipError_t launch_recompute_comps(const GridDev& g, const LigDev* d_lig,
                                   hipStream_t st);
 
 // MBAR kernels (mbar.hip).  One entry per problem of a batch, in device
-// memory; kernels take the table and a device list of problem indices and
-// put the list position in blockIdx.y.
+// memory, ordered by tile count; a launch covers a run of them, blockIdx.y
+// each.
+// What a problem waits for: the sums at its start, at a trial, at a
+// fixed-point update (whose values k_self_consistent forms first), nothing.
+enum MbarPhase : int {
+  kMbarStart = 0,
+  kMbarSearch = 1,
+  kMbarFixed = 2,
+  kMbarDone = 3
+};
+struct MbarState {
+  int phase;
+  int it;      // current iteration (1-based)
+  int ls;      // line-search trials made in this iteration
+  int n_iter;  // iterations taken, once done
+  double trust, Fcur, t, maxstep, gs;
+};
+// 16-row tiles of the weights' product, and the doubles of one block's
+// partial sums: the objective's sum (padded), column sums, then the lower
+// triangle's tiles
+constexpr int kMbarHead = 16;
+__host__ __device__ inline int mbar_tiles(int K) { return (K + 15) / 16; }
+__host__ __device__ inline int mbar_width(int K) {
+  const int nt = mbar_tiles(K);
+  return kMbarHead + 16 * nt + 256 * (nt * (nt + 1) / 2);
+}
 struct MbarProb {
   const double* ukn;  // K x N, leading dimension ld
   int64_t N, ld;
   int K;
-  int nb;             // blocks of the logD / objective pass
-  int nb_acc;         // blocks of the W W^T accumulation
-  int ts;             // register tile of the accumulation (mbar_acc_ts)
+  int nb;             // blocks of the pass over u_kn
   double* f;          // K current point (f_0 = 0)
   double* ftry;       // K line-search trial
   double* logN;       // K
   double* Nk;         // K
   double* logD;       // N
-  double* partial;    // max(nb, nb_acc) x (K + K*K)
-  double* red;        // K + K*K reduced sums
-  double* mat;        // (K-1) x (2K-1) augmented system (large K only)
+  double* partial;    // nb x mbar_width(K)
+  double* red;        // mbar_width(K) reduced sums
   double* step;       // K Newton step / fixed-point values
-  double* scalars;    // [0] objective [1] max|step| [2] g.step [3] status
-                      // [4] fixed-point change
   double* var;        // K variances
-  double* obj_part;   // nb
+  double* iter;       // iterations taken (result)
+  MbarState state;
 };
-int mbar_logD_blocks(int64_t N);
-int mbar_acc_ts(int K);
-int mbar_acc_blocks(int K, int64_t N);
-size_t mbar_newton_lds(int K, int want_inverse);
-// logD and scalars[0] at f (use_try = 0) or ftry
-hipError_t mbar_objective(const MbarProb* P, const int* list, int n,
-                          int max_nb, int use_try, hipStream_t st);
-// fixed-point update of f in place (logD current for f), change in [4]
-hipError_t mbar_fixed_point(const MbarProb* P, const int* list, int n,
-                            int max_K, hipStream_t st);
-// partial sums of W W^T at f; every listed problem has register tile ts
-hipError_t mbar_accumulate(const MbarProb* P, const int* list, int n, int ts,
-                           int max_blocks, hipStream_t st);
-// reduce the partial sums and solve for the Newton step (and variances)
-hipError_t mbar_newton(const MbarProb* P, const int* list, int n, int max_K,
-                       int want_inverse, hipStream_t st);
-hipError_t mbar_axpy(const MbarProb* P, const int* list, int n,
-                     const double* tvec, hipStream_t st);
-hipError_t mbar_accept(const MbarProb* P, const int* list, int n,
-                       hipStream_t st);
+constexpr int kMbarNarrow = 3;  // tiles a wavefront keeps to itself
+int mbar_blocks(int K, int64_t N);
+// One round: every problem's sums at the point its phase asks for (every
+// problem of the run has nt = mbar_tiles(K)) ...
+hipError_t mbar_sums(MbarProb* P, int n, int nt, int max_blocks,
+                     hipStream_t st);
+// ... their reduction ...
+hipError_t mbar_reduce(MbarProb* P, int n, int max_K, hipStream_t st);
+// ... the decision and the next step (every problem of the run has nt or
+// nt - 1 tiles, nt even); the last of the call's n_all problems to be done
+// (*n_done counts them) sets *host_done ...
+hipError_t mbar_step(MbarProb* P, int n, int nt, double tol, int max_iter,
+                     int* n_done, int n_all, volatile int* host_done,
+                     hipStream_t st);
+// ... and the fixed-point values of those whose Hessian was singular.
+hipError_t mbar_self_consistent(MbarProb* P, int n, int max_K,
+                                hipStream_t st);
 
 }  // namespace bpmf

@@ -266,3 +266,25 @@ def test_mbar_batch_equals_lone_solves():
         ctx.mbar_batch(us, bad)
     assert ctx.mbar_batch([], []) == []
     ctx.close()
+
+
+@pytest.mark.parametrize("K,per", [
+    (2, 2), (2, 700), (3, 43), (15, 17), (16, 8), (17, 9), (31, 33), (32, 64),
+    (33, 31), (47, 11), (48, 12), (49, 13), (63, 16), (64, 17), (65, 9),
+    (80, 5), (96, 11), (97, 6), (112, 8), (113, 7), (127, 9), (128, 12)])
+def test_mbar_tile_edges(K, per):
+    """One state short of, at and past every 16-state tile, both kernels of
+    the pass (up to three tiles and more) and every register block of the
+    solve, with sample counts that leave partial chunks: the free energies
+    and the last state's variance are the oracle's, to the tolerances of the
+    solves above (1e-7 kT, 1e-5 relative)."""
+    print_case("mbar tiles", K, per)
+    rng = np.random.default_rng([K, per])
+    u, Nk = _harmonic_problem(rng, K, per, 1.0 + 0.01 * K)
+    ctx = __import__("paper_1507_03703_amd").Context(seed=0)
+    f, var, it, f64, v64 = _mbar_both(ctx, u, Nk)
+    assert np.max(np.abs(f - f64)) < 1e-7 * max(1.0, np.abs(f64).max())
+    if np.isfinite(var[-1]):
+        assert abs(var[-1] / v64 - 1) < 1e-5
+    assert 0 < it < 200
+    ctx.close()
