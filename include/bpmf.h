@@ -471,7 +471,7 @@ BPMF_API int bpmf_proposal_grad(bpmf_ctx* ctx, int ligand_id,
 /* `steps` Adam steps (beta1 0.9, beta2 0.999, eps 1e-8, learning rate lr)
  * on minibatches of `batch` rows drawn with replacement (Philox) from the N
  * training pairs; loss_out (host, steps doubles, may be NULL) receives each
- * step's minibatch loss (synchronises every step when given). */
+ * step's minibatch loss (synchronises when given). */
 BPMF_API int bpmf_proposal_train(bpmf_ctx* ctx, int ligand_id,
                                  const float* dev_feats,
                                  const float* dev_poses, int64_t N, int batch,

@@ -77,7 +77,6 @@ struct LigHost {
   void* prop_arena = nullptr;
   PropDev* d_prop = nullptr;  // device copy of PropDev
   float* params = nullptr;    // kNParams fp32 master weights
-  float* grad = nullptr;      // kNParams
   float* adam_m = nullptr;
   float* adam_v = nullptr;
   int64_t adam_t = 0;
@@ -85,8 +84,8 @@ struct LigHost {
   // place in the batched pose-move tables (build_pose_tables): first task
   // (= first row), first forward group and their count
   int ptask0 = -1, pgroup0 = 0, n_pgroups = 0;
-  // bf16 transposed weights of the pose moves' forward pass (kTSize), stale
-  // while wt_dirty (after the fp32 parameters change)
+  // bf16 copies of the weights (kTSize), stale while wt_dirty (after the fp32
+  // parameters change; training keeps them up to date)
   unsigned short* wt = nullptr;
   bool wt_dirty = true;
   // intramolecular nonbonded / implicit-solvent terms (bpmf_pair_setup)
@@ -132,8 +131,10 @@ struct bpmf_ctx {
   int* mbar_flag = nullptr;  // pinned: set when a solve's last problem is done
   static constexpr int kMbarAhead = 3;  // rounds enqueued ahead of the device
   hipEvent_t mbar_round[kMbarAhead] = {};
-  void* mlp_mem = nullptr;   // activations of the proposal network
+  void* mlp_mem = nullptr;   // pose moves' network outputs
   size_t mlp_bytes = 0;
+  void* train_mem = nullptr;  // proposal training: activations, partial sums
+  size_t train_bytes = 0;
   void* place_mem = nullptr;  // centres of mass of placed configurations
   size_t place_bytes = 0;
   // this device's address of the no-allocation job table (or null)
@@ -424,6 +425,7 @@ extern "C" int bpmf_destroy(bpmf_ctx* c) {
     c->dfree(l.pair_arena);
   }
   c->dfree(c->mlp_mem);
+  c->dfree(c->train_mem);
   c->dfree(c->place_mem);
   c->dfree(c->grid_mem);
   c->dfree(c->d_ligs);
@@ -933,12 +935,8 @@ extern "C" int bpmf_ligand_setup(bpmf_ctx* c, const bpmf_ligand_desc* d,
 }
 
 namespace {
-// proposal network scratch (see mlp_scratch); pose moves of one ligand
-struct MlpBufs {
-  float *Z1, *H1, *Z2, *H2, *out, *dout, *dZ2, *dZ1, *bf, *bp;
-  double* loss_part;
-};
-int mlp_scratch(bpmf_ctx* c, int B, MlpBufs* b);
+// the batched pose moves' network outputs
+int pose_scratch(bpmf_ctx* c);
 int build_pose_tables(bpmf_ctx* c);
 int refresh_pose_weights(bpmf_ctx* c);
 int pair_sample_refresh(bpmf_ctx* c, int lid);
@@ -1150,8 +1148,7 @@ static int hmc_sweep_impl(bpmf_ctx* c, const bpmf_sweep_args* a, int only) {
     if (a->pose_move_every > 0) {
       if ((rc = build_pose_tables(c)) || (rc = refresh_pose_weights(c)))
         return rc;
-      MlpBufs b;
-      if (c->n_ptasks > 0 && (rc = mlp_scratch(c, c->n_ptasks, &b))) return rc;
+      if (c->n_ptasks > 0 && (rc = pose_scratch(c))) return rc;
     }
     const int units = a->n_sweeps / P, rest = a->n_sweeps % P;
     auto unit = [&](hipStream_t st) -> int {
@@ -2312,89 +2309,41 @@ extern "C" int bpmf_get_waves(bpmf_ctx* c, int ligand_id, int* waves) {
 // ============================================================================
 namespace {
 
+int pose_scratch(bpmf_ctx* c) {
+  return ensure_scratch(c, &c->mlp_mem, &c->mlp_bytes,
+                        (size_t)c->n_ptasks * kNOut * 4);
+}
 
-
-int mlp_scratch(bpmf_ctx* c, int B, MlpBufs* b) {
+// the training pass's scratch for B rows: activations, partial sums, and
+// `steps` losses (a step's each)
+int train_scratch(bpmf_ctx* c, int B, int steps, TrainArgs* t, float** split,
+                  double** loss) {
+  const int Bp = (B + 31) / 32 * 32, ns = train_splits(Bp);
   Arena A;
-  const size_t o_z1 = A.add((size_t)B * kNHid * 4), o_h1 = A.add((size_t)B * kNHid * 4),
-               o_z2 = A.add((size_t)B * kNHid * 4), o_h2 = A.add((size_t)B * kNHid * 4),
-               o_out = A.add((size_t)B * kNOut * 4), o_do = A.add((size_t)B * kNOut * 4),
-               o_dz2 = A.add((size_t)B * kNHid * 4), o_dz1 = A.add((size_t)B * kNHid * 4),
-               o_bf = A.add((size_t)B * kNFeat * 4), o_bp = A.add((size_t)B * 6 * 4),
-               o_lp = A.add((size_t)((B + 255) / 256) * 8);
-  int rc = ensure_scratch(c, &c->mlp_mem, &c->mlp_bytes, A.total);
+  const size_t o_act = A.add((size_t)kActRows * Bp * 2),
+               o_bias = A.add((size_t)(Bp / 16) * kNBias * 8),
+               o_lp = A.add((size_t)(Bp / 16) * 8),
+               o_split = A.add(ns > 1 ? (size_t)ns * kNParams * 4 : 0),
+               o_loss = A.add((size_t)steps * 8);
+  const int rc = ensure_scratch(c, &c->train_mem, &c->train_bytes, A.total);
   if (rc) return rc;
-  char* base = (char*)c->mlp_mem;
-  b->Z1 = (float*)(base + o_z1);
-  b->H1 = (float*)(base + o_h1);
-  b->Z2 = (float*)(base + o_z2);
-  b->H2 = (float*)(base + o_h2);
-  b->out = (float*)(base + o_out);
-  b->dout = (float*)(base + o_do);
-  b->dZ2 = (float*)(base + o_dz2);
-  b->dZ1 = (float*)(base + o_dz1);
-  b->bf = (float*)(base + o_bf);
-  b->bp = (float*)(base + o_bp);
-  b->loss_part = (double*)(base + o_lp);
+  char* base = (char*)c->train_mem;
+  t->B = B;
+  t->Bp = Bp;
+  t->inv_b = 1.0f / (float)B;
+  t->act = (unsigned short*)(base + o_act);
+  t->biasP = (double*)(base + o_bias);
+  t->lossP = (double*)(base + o_lp);
+  *split = (float*)(base + o_split);
+  *loss = (double*)(base + o_loss);
   return BPMF_OK;
 }
 
-GemmArgs gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak,
-              const float* B, int64_t sbk, int64_t sbn, float* C, int64_t ldc,
-              const float* bias, int epi, float* Zout, const float* Zin) {
-  GemmArgs g;
-  g.M = M; g.N = N; g.K = K;
-  g.A = A; g.sam = sam; g.sak = sak;
-  g.B = B; g.sbk = sbk; g.sbn = sbn;
-  g.C = C; g.ldc = ldc; g.bias = bias; g.epi = epi; g.Zout = Zout; g.Zin = Zin;
-  return g;
-}
-
-// out = MLP(feats) for B rows
-int mlp_forward(bpmf_ctx* c, const float* P, const float* feats, int B,
-                const MlpBufs& b, float* out, hipStream_t st) {
-  HIP_TRY(launch_mlp_forward(P, feats, B, b.Z1, b.H1, b.Z2, b.H2, out, st));
-  return BPMF_OK;
-}
-
-// gradient of the mean NLL of (feats, poses) into G; loss partials in b
-int mlp_grad(bpmf_ctx* c, const float* P, const float* feats,
-             const float* poses, int B, const MlpBufs& b, float* G) {
-  int rc = mlp_forward(c, P, feats, B, b, b.out, c->stream);
-  if (rc) return rc;
-  HIP_TRY(launch_nll(b.out, poses, B, b.dout, b.loss_part, c->stream));
-  // dZ2 = (dout W3^T) * silu'(Z2); dZ1 = (dZ2 W2^T) * silu'(Z1)
-  HIP_TRY(launch_gemm(gemm(B, kNHid, kNOut, b.dout, kNOut, 1, P + kOffW3, 1,
-                           kNOut, b.dZ2, kNHid, nullptr, kEpiDsilu, nullptr, b.Z2),
-                      c->stream));
-  HIP_TRY(launch_gemm(gemm(B, kNHid, kNHid, b.dZ2, kNHid, 1, P + kOffW2, 1, kNHid,
-                           b.dZ1, kNHid, nullptr, kEpiDsilu, nullptr, b.Z1),
-                      c->stream));
-  // weight gradients: H2^T dout, H1^T dZ2, feats^T dZ1
-  HIP_TRY(launch_gemm(gemm(kNHid, kNOut, B, b.H2, 1, kNHid, b.dout, kNOut, 1,
-                           G + kOffW3, kNOut, nullptr, kEpiStore, nullptr, nullptr),
-                      c->stream));
-  HIP_TRY(launch_gemm(gemm(kNHid, kNHid, B, b.H1, 1, kNHid, b.dZ2, kNHid, 1,
-                           G + kOffW2, kNHid, nullptr, kEpiStore, nullptr, nullptr),
-                      c->stream));
-  HIP_TRY(launch_gemm(gemm(kNFeat, kNHid, B, feats, 1, kNFeat, b.dZ1, kNHid, 1,
-                           G + kOffW1, kNHid, nullptr, kEpiStore, nullptr, nullptr),
-                      c->stream));
-  HIP_TRY(launch_colsum(b.dout, B, kNOut, kNOut, G + kOffB3, c->stream));
-  HIP_TRY(launch_colsum(b.dZ2, B, kNHid, kNHid, G + kOffB2, c->stream));
-  HIP_TRY(launch_colsum(b.dZ1, B, kNHid, kNHid, G + kOffB1, c->stream));
-  return BPMF_OK;
-}
-
-int read_loss(bpmf_ctx* c, const MlpBufs& b, int B, double* loss) {
-  const int nb = (B + 255) / 256;
-  std::vector<double> lp(nb);
-  HIP_TRY(hipMemcpyAsync(lp.data(), b.loss_part, nb * 8, hipMemcpyDeviceToHost,
-                         c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  double s = 0.0;
-  for (double v : lp) s += v;
-  *loss = s / B;
+// the ligand's bf16 weight copies, when its fp32 parameters have changed
+int refresh_weights(bpmf_ctx* c, LigHost& h) {
+  if (!h.wt_dirty) return BPMF_OK;
+  HIP_TRY(launch_weights_bf16(h.params, h.wt, c->stream));
+  h.wt_dirty = false;
   return BPMF_OK;
 }
 
@@ -2436,7 +2385,7 @@ extern "C" int bpmf_proposal_setup(bpmf_ctx* c, int lid, const int* frame_atoms,
     if (!isfinite(params[q])) return fail(BPMF_E_INVAL, "non-finite parameter");
   const int K = h.dev.K;
   Arena A;
-  const size_t o_p = A.add(kNParams * 4), o_g = A.add(kNParams * 4),
+  const size_t o_p = A.add(kNParams * 4),
                o_m = A.add(kNParams * 4), o_v = A.add(kNParams * 4),
                o_acc = A.add(K * 8), o_try = A.add(K * 8), o_la = A.add(K * 8),
                o_dev = A.add(sizeof(PropDev)),
@@ -2470,7 +2419,6 @@ extern "C" int bpmf_proposal_setup(bpmf_ctx* c, int lid, const int* frame_atoms,
   c->dfree(h.prop_arena);
   h.prop_arena = base;
   h.params = (float*)(base + o_p);
-  h.grad = (float*)(base + o_g);
   h.adam_m = (float*)(base + o_m);
   h.adam_v = (float*)(base + o_v);
   h.d_prop = (PropDev*)(base + o_dev);
@@ -2525,10 +2473,11 @@ extern "C" int bpmf_proposal_forward(bpmf_ctx* c, int lid,
   if (N < 0 || N > (1 << 24)) return fail(BPMF_E_INVAL, "N outside 0..2^24");
   if (N == 0) return BPMF_OK;
   if (!dev_feats || !dev_out) return fail(BPMF_E_INVAL, "null argument");
-  MlpBufs b;
-  if ((rc = mlp_scratch(c, (int)N, &b))) return rc;
-  return mlp_forward(c, c->ligs[lid].params, dev_feats, (int)N, b, dev_out,
-                     c->stream);
+  LigHost& h = c->ligs[lid];
+  if ((rc = refresh_weights(c, h))) return rc;
+  HIP_TRY(launch_mlp_forward(h.params, h.wt, dev_feats, (int)N, dev_out,
+                             c->stream));
+  return BPMF_OK;
 }
 
 extern "C" int bpmf_proposal_grad(bpmf_ctx* c, int lid, const float* dev_feats,
@@ -2540,12 +2489,26 @@ extern "C" int bpmf_proposal_grad(bpmf_ctx* c, int lid, const float* dev_feats,
   if (N < 1 || N > (1 << 24)) return fail(BPMF_E_INVAL, "N outside 1..2^24");
   if (!dev_feats || !dev_poses || !dev_grad)
     return fail(BPMF_E_INVAL, "null argument");
-  MlpBufs b;
-  if ((rc = mlp_scratch(c, (int)N, &b))) return rc;
-  if ((rc = mlp_grad(c, c->ligs[lid].params, dev_feats, dev_poses, (int)N, b,
-                     dev_grad)))
-    return rc;
-  if (loss) return read_loss(c, b, (int)N, loss);
+  LigHost& h = c->ligs[lid];
+  if ((rc = refresh_weights(c, h))) return rc;
+  TrainArgs t{};
+  float* split;
+  double* d_loss;
+  if ((rc = train_scratch(c, (int)N, 1, &t, &split, &d_loss))) return rc;
+  t.P = h.params;
+  t.WT = h.wt;
+  t.feats = dev_feats;
+  t.poses = dev_poses;
+  t.N = N;
+  AdamArgs w{};
+  w.G = dev_grad;
+  HIP_TRY(launch_train_step(t, w, split, d_loss, c->stream));
+  if (loss) {
+    double s = 0.0;
+    HIP_TRY(hipMemcpyAsync(&s, d_loss, 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    *loss = s / (double)N;
+  }
   return BPMF_OK;
 }
 
@@ -2558,21 +2521,47 @@ extern "C" int bpmf_proposal_train(bpmf_ctx* c, int lid, const float* dev_feats,
   if (N < 1 || batch < 1 || batch > (1 << 20) || steps < 0 || !(lr > 0))
     return fail(BPMF_E_INVAL, "bad training arguments");
   if (!dev_feats || !dev_poses) return fail(BPMF_E_INVAL, "null data");
+  if (steps == 0) return BPMF_OK;
   LigHost& h = c->ligs[lid];
-  MlpBufs b;
-  if ((rc = mlp_scratch(c, batch, &b))) return rc;
-  if (steps > 0) h.wt_dirty = true;
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  if ((rc = refresh_weights(c, h))) return rc;
+  // the losses of up to kLossSteps steps are read back together
+  constexpr int kLossSteps = 1024;
+  TrainArgs t{};
+  float* split;
+  double* d_loss;
+  if ((rc = train_scratch(c, batch, std::min(steps, kLossSteps), &t, &split,
+                          &d_loss)))
+    return rc;
+  t.P = h.params;
+  t.WT = h.wt;
+  t.feats = dev_feats;
+  t.poses = dev_poses;
+  t.N = N;
+  t.gather = true;
+  t.seed = c->seed;
+  AdamArgs w{};
+  w.P = h.params;
+  w.m = h.adam_m;
+  w.v = h.adam_v;
+  w.lr = (float)lr;
+  w.b1 = 0.9f;
+  w.b2 = 0.999f;
+  w.eps = 1e-8f;
   for (int s = 0; s < steps; ++s) {
-    HIP_TRY(launch_gather_batch(dev_feats, dev_poses, N, batch, c->seed,
-                                (uint64_t)h.adam_t, b.bf, b.bp, c->stream));
-    if ((rc = mlp_grad(c, h.params, b.bf, b.bp, batch, b, h.grad))) return rc;
+    t.step = (uint64_t)h.adam_t;
     ++h.adam_t;
-    const float c1 = 1.f - powf(b1, (float)h.adam_t);
-    const float c2 = 1.f - powf(b2, (float)h.adam_t);
-    HIP_TRY(launch_adam(h.params, h.grad, h.adam_m, h.adam_v, kNParams,
-                        (float)lr, b1, b2, eps, c1, c2, c->stream));
-    if (loss_out && (rc = read_loss(c, b, batch, &loss_out[s]))) return rc;
+    w.c1 = 1.f - powf(w.b1, (float)h.adam_t);
+    w.c2 = 1.f - powf(w.b2, (float)h.adam_t);
+    HIP_TRY(launch_train_step(t, w, split, d_loss + s % kLossSteps,
+                              c->stream));
+    const int have = s % kLossSteps + 1;
+    if (loss_out && (have == kLossSteps || s + 1 == steps)) {
+      double* out = loss_out + (s + 1 - have);
+      HIP_TRY(hipMemcpyAsync(out, d_loss, (size_t)have * 8,
+                             hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));
+      for (int q = 0; q < have; ++q) out[q] /= (double)batch;
+    }
   }
   return BPMF_OK;
 }
@@ -2647,9 +2636,9 @@ int build_pose_tables(bpmf_ctx* c) {
 // called outside graph capture, before the moves that read them).
 int refresh_pose_weights(bpmf_ctx* c) {
   for (auto& h : c->ligs)
-    if (h.has_prop && h.wt_dirty) {
-      HIP_TRY(launch_weights_bf16(h.params, h.wt, c->stream));
-      h.wt_dirty = false;
+    if (h.has_prop) {
+      const int rc = refresh_weights(c, h);
+      if (rc) return rc;
     }
   return BPMF_OK;
 }
@@ -2677,12 +2666,12 @@ int pose_move_batch(bpmf_ctx* c, int only, hipStream_t st,
     ng = h.n_pgroups;
   }
   if (nt == 0) return BPMF_OK;
-  MlpBufs b;
-  int rc = mlp_scratch(c, c->n_ptasks, &b);
+  const int rc = pose_scratch(c);
   if (rc) return rc;
+  float* out = (float*)c->mlp_mem;
   const int n_fin = close ? close->l1 - close->l0 : 0;
   HIP_TRY(launch_pose_network(
-      c->d_pgroups + g0, ng, c->d_ligs, c->d_props, c->d_ptasks, b.out,
+      c->d_pgroups + g0, ng, c->d_ligs, c->d_props, c->d_ptasks, out,
       close ? c->d_ligs + close->l0 : nullptr, n_fin,
       close ? close->exchange_every : 0, close ? close->sample_every : 0,
       c->seed, st));
@@ -2696,7 +2685,7 @@ int pose_move_batch(bpmf_ctx* c, int only, hipStream_t st,
     if (e > a) qmax = q;
   }
   HIP_TRY(launch_pose_move(c->grid, c->d_ligs, c->d_props, c->d_ptasks + t0,
-                           nt, b.out, 1 << qmax,
+                           nt, out, 1 << qmax,
                            block_lds_bytes(1 << qmax, false, 0, 0, 0, 0),
                            c->seed, close != nullptr, st));
   return BPMF_OK;

@@ -23,7 +23,7 @@ constexpr int kOffW3 = kOffB2 + kNHid;
 constexpr int kOffB3 = kOffW3 + kNHid * kNOut;
 constexpr int kNParams = kOffB3 + kNOut;
 
-// bf16 copy of the weights for the pose moves' forward pass, each matrix
+// bf16 copy of the weights for the forward pass, each matrix
 // transposed ([out][in]) with rows padded so that a lane's eight
 // consecutive k values are one 16-byte load and every 16-column output tile
 // is in range: W1^T 256 x 32, W2^T 256 x 256, W3^T 112 x 256 (padding 0)
@@ -31,7 +31,19 @@ constexpr int kT1Ld = 32, kT2Ld = kNHid, kT3Ld = kNHid, kT3Rows = 112;
 constexpr int kTOff1 = 0;
 constexpr int kTOff2 = kTOff1 + kNHid * kT1Ld;
 constexpr int kTOff3 = kTOff2 + kNHid * kT2Ld;
-constexpr int kTSize = kTOff3 + kT3Rows * kT3Ld;
+// the same of W2 and W3 row by row, for the backward pass: W2 256 x 256, W3
+// 256 x 128 (padding 0)
+constexpr int kR3Ld = 128;
+constexpr int kTOffR2 = kTOff3 + kT3Rows * kT3Ld;
+constexpr int kTOffR3 = kTOffR2 + kNHid * kNHid;
+constexpr int kTSize = kTOffR3 + kNHid * kR3Ld;
+
+// rows of a minibatch's transposed bf16 activations (Bp elements each):
+// features, H1, H2, dout, dZ2, dZ1; and the biases (b1, b2, b3)
+constexpr int kActF = 0, kActH1 = kNFeat, kActH2 = kActH1 + kNHid,
+              kActD = kActH2 + kNHid, kActZ2 = kActD + kT3Rows,
+              kActZ1 = kActZ2 + kNHid, kActRows = kActZ1 + kNHid;
+constexpr int kNBias = 2 * kNHid + kNOut;
 
 enum Purpose2 : uint32_t { kPose = 4, kBatch = 5 };
 
@@ -56,43 +68,43 @@ struct PoseTask {
 // most 16) through the network whose parameters start at P.
 struct MlpGroup {
   const float* P;             // fp32 parameters (the biases are read here)
-  const unsigned short* WT;   // bf16 transposed weights (kTSize)
+  const unsigned short* WT;   // bf16 weights (kTSize)
   int row0, rows;
 };
 
-enum { kEpiStore = 0, kEpiSilu = 1, kEpiDsilu = 2 };
-
-// C[m, n] = sum_k A(m, k) B(k, n) (+ bias[n]); A(m, k) = A[m*sam + k*sak],
-// B(k, n) = B[k*sbk + n*sbn]; bf16 operands, fp32 accumulation.
-// kEpiSilu: Zout = acc + bias, C = silu(Zout).  kEpiDsilu: C = acc *
-// silu'(Zin).  Row stride of C, Zout, Zin: ldc.
-struct GemmArgs {
-  int M, N, K;
-  const float* A;
-  int64_t sam, sak;
-  const float* B;
-  int64_t sbk, sbn;
-  float* C;
-  int64_t ldc;
-  const float* bias;
-  int epi;
-  float* Zout;
-  const float* Zin;
+// One gradient of the mean negative log-likelihood over B rows (Bp: rounded
+// up to 32).  gather: row i is training row philox(step, i) mod N of feats
+// and poses; else row i.
+struct TrainArgs {
+  const float* P;          // fp32 parameters (the biases are read here)
+  unsigned short* WT;      // bf16 copies of the weights (kTSize)
+  const float* feats;      // N x kNFeat
+  const float* poses;      // N x 6
+  int64_t N;
+  int B, Bp;
+  bool gather;
+  uint64_t seed, step;
+  float inv_b;             // 1 / B
+  unsigned short* act;     // kActRows x Bp transposed activations
+  double* biasP;           // Bp / 16 x kNBias column sums per row block
+  double* lossP;           // Bp / 16 loss sums per row block
 };
-
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t st);
-// the whole network for B rows (features B x kNFeat): Z1, H1, Z2, H2 (B x
-// kNHid) and out (B x kNOut), equal to three launch_gemm calls
-hipError_t launch_mlp_forward(const float* P, const float* X, int B,
-                              float* Z1, float* H1, float* Z2, float* H2,
-                              float* out, hipStream_t st);
-hipError_t launch_colsum(const float* X, int rows, int cols, int64_t ld,
-                         float* out, hipStream_t st);
-hipError_t launch_nll(const float* out, const float* pose, int B, float* dout,
-                      double* loss_part, hipStream_t st);
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n,
-                       float lr, float b1, float b2, float eps, float c1,
-                       float c2, hipStream_t st);
+// Where a gradient goes: into G, or (G null) into an Adam step of P with
+// moments m and v (c1, c2: the bias corrections)
+struct AdamArgs {
+  float* G;
+  float *P, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+// out = network(X) for B rows (features B x kNFeat, outputs B x kNOut)
+hipError_t launch_mlp_forward(const float* P, const unsigned short* WT,
+                              const float* X, int B, float* out,
+                              hipStream_t st);
+// one gradient or Adam step; *loss (device) = the rows' summed loss; split:
+// train_splits(Bp) x kNParams floats when that is more than one
+int train_splits(int Bp);
+hipError_t launch_train_step(const TrainArgs& a, const AdamArgs& w,
+                             float* split, double* loss, hipStream_t st);
 hipError_t launch_pose_features(const LigDev* lig, const PropDev* prop,
                                 const float* xs, int64_t N, float* feats,
                                 float* poses, hipStream_t st);
@@ -106,7 +118,7 @@ hipError_t launch_pose_network(const MlpGroup* groups, int n_groups,
                                const LigDev* fin, int n_fin,
                                int exchange_every, int sample_every,
                                uint64_t seed, hipStream_t st);
-// the bf16 transposed copy of the weights of parameter vector P
+// the bf16 copies of the weights of parameter vector P
 hipError_t launch_weights_bf16(const float* P, unsigned short* WT,
                                hipStream_t st);
 // one pose move of each of the n tasks (all of `waves` wavefronts; props
@@ -117,9 +129,5 @@ hipError_t launch_pose_move(const GridDev& g, const LigDev* ligs,
                             const PropDev* props, const PoseTask* tasks,
                             int n, const float* out, int waves, int lds,
                             uint64_t seed, bool begin_next, hipStream_t st);
-hipError_t launch_gather_batch(const float* feats, const float* poses,
-                               int64_t N, int B, uint64_t seed,
-                               uint64_t step, float* bf, float* bp,
-                               hipStream_t st);
 
 }  // namespace bpmf

@@ -7,10 +7,13 @@
 // the acceptance carries the exact proposal density on SE(3).
 //
 // Dense layers run on the matrix cores: v_mfma_f32_16x16x32_bf16 with bf16
-// operands rounded from fp32 when they are staged in LDS and fp32
-// accumulation.
+// operands rounded from fp32 (activations when they are formed, weights when
+// they change) and fp32 accumulation.
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "deferred.h"
 #include "device.h"
@@ -32,7 +35,6 @@ __device__ __forceinline__ unsigned short bf16_bits(float f) {
   return (unsigned short)((u & 0x7fffffffu) > 0x7f800000u ? qn : rn);
 }
 
-constexpr int kTile = 64;   // output tile edge per workgroup
 constexpr int kKStep = 32;  // K per MFMA
 constexpr int kPad = 8;     // LDS row padding (bf16 elements)
 
@@ -42,165 +44,58 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// C[m, n] = sum_k A(m, k) B(k, n) with epilogue (see GemmArgs).  A block of
-// 256 threads computes a 64 x 64 tile; wave (wm, wn) owns a 32 x 32 quarter
-// as 2 x 2 MFMA tiles of 16 x 16.  Operand layout of the 16x16x32 bf16 MFMA:
-// lane l supplies row (l % 16) of A and column (l % 16) of B, each with the
-// 8 consecutive k = 8 (l / 16) .. + 7; it receives D rows 4 (l / 16) .. + 3
-// of column l % 16.
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ __align__(16) unsigned short As[kTile][kKStep + kPad];
-  __shared__ __align__(16) unsigned short Bs[kTile][kKStep + kPad];  // [n][k]
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int k0 = 0; k0 < g.K; k0 += kKStep) {
-    // stage: 64 x 32 elements of A and of B, 8 per thread
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = tid + 256 * q;       // 0 .. 2047
-      const int r = e >> 5, kk = e & 31;  // row/col of tile, k in step
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      float av = 0.f, bv = 0.f;
-      if (m < g.M && k < g.K) av = g.A[(int64_t)m * g.sam + (int64_t)k * g.sak];
-      if (n < g.N && k < g.K) bv = g.B[(int64_t)k * g.sbk + (int64_t)n * g.sbn];
-      As[r][kk] = bf16_bits(av);
-      Bs[r][kk] = bf16_bits(bv);
-    }
-    __syncthreads();
-    const int kg = (lane >> 4) * 8;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int ar = wm * 32 + i * 16 + (lane & 15);
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(&As[ar][kg]);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int bc = wn * 32 + j * 16 + (lane & 15);
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Bs[bc][kg]);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i][j], 0,
-                                                            0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  // epilogue
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m = m0 + wm * 32 + i * 16 + (lane >> 4) * 4 + q;
-        const int n = n0 + wn * 32 + j * 16 + (lane & 15);
-        if (m >= g.M || n >= g.N) continue;
-        float v = acc[i][j][q];
-        const int64_t o = (int64_t)m * g.ldc + n;
-        if (g.bias) v += g.bias[n];
-        if (g.epi == kEpiSilu) {
-          g.Zout[o] = v;
-          g.C[o] = silu(v);
-        } else if (g.epi == kEpiDsilu) {
-          g.C[o] = v * dsilu(g.Zin[o]);
-        } else {
-          g.C[o] = v;
-        }
-      }
-}
-
 // The three dense layers for kFRows rows per workgroup.  A row's path
 // through the network does not involve the other rows, so one workgroup
-// takes its rows through all three layers with the activations held in LDS
-// as the next layer's bf16 operand; each wave owns every kFWaves-th
-// 16-column output tile.  Every tile is accumulated by the same MFMA over the same
-// 32-wide k chunks in the same order, from operands rounded to bf16 in the
-// same way, and finished by the same epilogue as k_gemm, so the outputs are
-// those of three k_gemm launches.
+// takes its rows through all layers with the activations held in LDS as the
+// next layer's bf16 operand; each wave owns every kFWaves-th 16-column output
+// tile.
 constexpr int kFRows = 16;
 constexpr int kFWaves = 16;  // wavefronts per workgroup
 constexpr int kFLd = kNHid + kPad;  // LDS row length (bf16 elements)
 
-// one layer: out(16 x N) = act(A(16 x Kin) W(Kin x N) + bias), A in LDS.
-// A wave accumulates all its tiles in one pass over k, so the weight loads
-// of every tile of a k chunk are in flight together.
-template <int KIN, int N, bool HIDDEN>
-__device__ __forceinline__ void dense_rows(
-    const unsigned short (*A)[kFLd], const float* __restrict__ W,
-    const float* __restrict__ bias, int row0, int B, float* __restrict__ Z,
-    float* __restrict__ H, unsigned short (*Hn)[kFLd], int lane, int wv) {
-  constexpr int kTiles = (N + 15) / 16;
-  constexpr int kTPW = (kTiles + kFWaves - 1) / kFWaves;
+// Operand layout of the 16x16x32 bf16 MFMA: lane l supplies row (l % 16) of A
+// and column (l % 16) of B, each with the 8 consecutive k = 8 (l / 16) .. + 7;
+// it receives D rows 4 (l / 16) .. + 3 of column l % 16.
+
+// One 16 x 16 tile of A(16 x KIN) B: A in LDS (rows of LDA, valid below KV),
+// b = the lane's first element of its column's KLD-long bf16 row.  k ascends
+// in chunks of 32.  The B loads (every chunk's, one 16-byte load each) can be
+// issued by tile_load before the barrier that completes A.
+template <int KIN>
+struct TileB {
+  bf16x8 v[KIN / kKStep];
+};
+template <int KIN>
+__device__ __forceinline__ void tile_load(const unsigned short* b,
+                                          TileB<KIN>& t) {
+  typedef const bf16x8 __attribute__((address_space(1))) gbf;
+#pragma unroll
+  for (int q = 0; q < KIN / kKStep; ++q) t.v[q] = *(gbf*)(b + kKStep * q);
+}
+template <int KIN, int KV, int LDA>
+__device__ __forceinline__ f32x4 tile_mul(const unsigned short (*A)[LDA],
+                                          const TileB<KIN>& t, int lane) {
   const int kg = (lane >> 4) * 8;
-  f32x4 acc[kTPW];
+  f32x4 acc{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < kTPW; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-  for (int k0 = 0; k0 < KIN; k0 += kKStep) {
-    bf16x8 a, b[kTPW];
-    // loads at clamped (in-bounds) indices, unconditionally, so that they
-    // issue together; out-of-range operands are then zeroed
-    float w[kTPW][8];
-    unsigned short av[8];
+  for (int q = 0; q < KIN / kKStep; ++q) {
+    bf16x8 a;
+    if (KV % kKStep == 0 || kKStep * q + kg < KV) {
+      a = *reinterpret_cast<const bf16x8*>(&A[lane & 15][kKStep * q + kg]);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = k0 + kg + e, kc = k < KIN ? k : KIN - 1;
-      av[e] = A[lane & 15][kc];
-#pragma unroll
-      for (int i = 0; i < kTPW; ++i) {
-        const int n = (wv + kFWaves * i) * 16 + (lane & 15);
-        const int nc = n < N ? n : N - 1;
-        w[i][e] = W[(int64_t)kc * N + nc];
-      }
+      for (int e = 0; e < 8; ++e)
+        a[e] = __builtin_bit_cast(__bf16, (unsigned short)0);
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool in = k0 + kg + e < KIN;
-      a[e] = __builtin_bit_cast(__bf16, in ? av[e] : (unsigned short)0);
-#pragma unroll
-      for (int i = 0; i < kTPW; ++i) {
-        const int n = (wv + kFWaves * i) * 16 + (lane & 15);
-        b[i][e] = __builtin_bit_cast(
-            __bf16, (in && n < N) ? bf16_bits(w[i][e]) : (unsigned short)0);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kTPW; ++i)
-      if (wv + kFWaves * i < kTiles)  // uniform over the wave
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[i], acc[i], 0,
-                                                         0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, t.v[q], acc, 0, 0, 0);
   }
-#pragma unroll
-  for (int i = 0; i < kTPW; ++i) {
-    const int n = (wv + kFWaves * i) * 16 + (lane & 15);
-    if (n >= N) continue;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = (lane >> 4) * 4 + q, m = row0 + r;
-      const float v = acc[i][q] + bias[n];
-      if (HIDDEN) {
-        const float h = silu(v);
-        Hn[r][n] = bf16_bits(h);
-        if (m < B) {
-          Z[(int64_t)m * N + n] = v;
-          H[(int64_t)m * N + n] = h;
-        }
-      } else if (m < B) {
-        H[(int64_t)m * N + n] = v;
-      }
-    }
-  }
+  return acc;
 }
 
-// dense_rows with the weights from their bf16 transposed copy (row n of WT
-// holds column n of W, KLD elements, zero past KIN and past N): a lane's
-// eight k values of a tile are one 16-byte load.  The operands, the k order
-// and the epilogue are dense_rows', so the results are the same bits.
+// One layer: out(16 x N) = act(A(16 x KIN) W + bias), the weights from their
+// bf16 transposed copy (row n of WT holds column n of W, KLD elements, zero
+// past KIN and past N): a lane's eight k values of a tile are one 16-byte
+// load.
 template <int KIN, int KLD, int N, bool HIDDEN>
 __device__ __forceinline__ void dense_rows_t(
     const unsigned short (*A)[kFLd], const unsigned short* __restrict__ WT,
@@ -311,29 +206,38 @@ __global__ __launch_bounds__(kFWaves * 64) void k_pose_network(
 }
 
 // WT from the fp32 parameters: element (n, k) of each transposed matrix is
-// the bf16 rounding of W[k][n] (0 in the padding)
+// the bf16 rounding of W[k][n] (0 in the padding); then the same of W2 and W3
+// row by row
 __global__ __launch_bounds__(256) void k_weights_bf16(
     const float* __restrict__ P, unsigned short* __restrict__ WT) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= kTSize) return;
   int off, ld, kin, nout;
   const float* W;
+  bool rows = false;
   if (i < kTOff2) {
     off = kTOff1; ld = kT1Ld; kin = kNFeat; nout = kNHid; W = P + kOffW1;
   } else if (i < kTOff3) {
     off = kTOff2; ld = kT2Ld; kin = kNHid; nout = kNHid; W = P + kOffW2;
-  } else {
+  } else if (i < kTOffR2) {
     off = kTOff3; ld = kT3Ld; kin = kNHid; nout = kNOut; W = P + kOffW3;
+  } else if (i < kTOffR3) {
+    off = kTOffR2; ld = kNHid; kin = kNHid; nout = kNHid; W = P + kOffW2;
+    rows = true;
+  } else {
+    off = kTOffR3; ld = kR3Ld; kin = kNHid; nout = kNOut; W = P + kOffW3;
+    rows = true;
   }
-  const int n = (i - off) / ld, k = (i - off) - n * ld;
+  const int a = (i - off) / ld, b = (i - off) - a * ld;
+  const int n = rows ? b : a, k = rows ? a : b;
   WT[i] = (n < nout && k < kin) ? bf16_bits(W[(int64_t)k * nout + n])
                                 : (unsigned short)0;
 }
 
+// network outputs of B rows of features
 __global__ __launch_bounds__(kFWaves * 64) void k_mlp_forward(
-    const float* __restrict__ P, const float* __restrict__ X, int B,
-    float* __restrict__ Z1, float* __restrict__ H1, float* __restrict__ Z2,
-    float* __restrict__ H2, float* __restrict__ out) {
+    const float* __restrict__ P, const unsigned short* __restrict__ WT,
+    const float* __restrict__ X, int B, float* __restrict__ out) {
   __shared__ __align__(16) unsigned short S[2][kFRows][kFLd];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int row0 = blockIdx.x * kFRows;
@@ -342,42 +246,21 @@ __global__ __launch_bounds__(kFWaves * 64) void k_mlp_forward(
     S[0][r][k] = bf16_bits(m < B ? X[(int64_t)m * kNFeat + k] : 0.f);
   }
   __syncthreads();
-  dense_rows<kNFeat, kNHid, true>(S[0], P + kOffW1, P + kOffB1, row0, B, Z1,
-                                  H1, S[1], lane, wv);
+  dense_rows_t<kNFeat, kT1Ld, kNHid, true>(S[0], WT + kTOff1, P + kOffB1,
+                                           row0, B, nullptr, S[1], lane, wv);
   __syncthreads();
-  dense_rows<kNHid, kNHid, true>(S[1], P + kOffW2, P + kOffB2, row0, B, Z2,
-                                 H2, S[0], lane, wv);
+  dense_rows_t<kNHid, kT2Ld, kNHid, true>(S[1], WT + kTOff2, P + kOffB2, row0,
+                                          B, nullptr, S[0], lane, wv);
   __syncthreads();
-  dense_rows<kNHid, kNOut, false>(S[0], P + kOffW3, P + kOffB3, row0, B,
-                                  nullptr, out, nullptr, lane, wv);
-}
-
-// column sums of X (rows x cols, row stride ld): out[c] = sum_r X[r, c].
-// 64 columns per block, each summed by 4 threads over interleaved rows and
-// the 4 partials added in a fixed order.
-__global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ X,
-                                                int rows, int cols, int64_t ld,
-                                                float* __restrict__ out) {
-  __shared__ double part[4][64];
-  const int cl = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
-  double s = 0.0;
-  if (c < cols) {
-#pragma unroll 8
-    for (int r = g; r < rows; r += 4) s += X[(int64_t)r * ld + c];
-  }
-  part[g][cl] = s;
-  __syncthreads();
-  if (g == 0 && c < cols)
-    out[c] = (float)(((part[0][cl] + part[1][cl]) + part[2][cl]) + part[3][cl]);
+  dense_rows_t<kNHid, kT3Ld, kNOut, false>(S[0], WT + kTOff3, P + kOffB3,
+                                           row0, B, out, nullptr, lane, wv);
 }
 
 __device__ __forceinline__ float sigm(float z) { return 1.0f / (1.0f + expf(-z)); }
 
 // Mixture parameters of one output row (13 numbers per component).
 struct Mix {
-  float lw[kNComp];  // log weights (normalised by mixture_of; the pose move
-                     // keeps the raw logits and normalises them, mix_lse)
+  float lw[kNComp];  // raw logits (mix_lse normalises them)
   float mt[kNComp][3], mw[kNComp][3], st[kNComp][3], sw[kNComp][3];
 };
 
@@ -390,100 +273,412 @@ __device__ __forceinline__ float mix_lse(const Mix& p) {
   return mx + logf(sm);
 }
 
-__device__ __forceinline__ void mixture_of(const float* o, Mix& p) {
-  float mx = -INFINITY;
-  for (int j = 0; j < kNComp; ++j) mx = fmaxf(mx, o[13 * j]);
-  float s = 0.f;
-  for (int j = 0; j < kNComp; ++j) s += expf(o[13 * j] - mx);
-  const float lse = mx + logf(s);
-  for (int j = 0; j < kNComp; ++j) {
-    const float* r = o + 13 * j;
-    p.lw[j] = r[0] - lse;
-    for (int a = 0; a < 3; ++a) {
-      p.mt[j][a] = r[1 + a];
-      p.mw[j][a] = (float)M_PI * tanhf(r[4 + a]);
-      p.st[j][a] = kSt0 + (kSt1 - kSt0) * sigm(r[7 + a]);
-      p.sw[j][a] = kSw0 + (kSw1 - kSw0) * sigm(r[10 + a]);
-    }
-  }
+// ----------------------------------------------------------------------------
+// training: the gradient of the mean negative log-likelihood, Adam
+// ----------------------------------------------------------------------------
+// columns of the transposed activations a row block leaves for the weight
+// gradients, by matrix
+__device__ __forceinline__ unsigned short* act_of(const TrainArgs& a, int row) {
+  return a.act + (int64_t)row * a.Bp;
 }
 
-// negative log-likelihood of (t, w) and d loss / d out (scaled by 1/B)
-__global__ __launch_bounds__(256) void k_nll(const float* __restrict__ out,
-                                             const float* __restrict__ pose,
-                                             int B, float inv_b,
-                                             float* __restrict__ dout,
-                                             double* __restrict__ loss_part) {
-  __shared__ double red[256];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  double li = 0.0;
-  if (i < B) {
-    const float* o = out + (int64_t)i * kNOut;
-    const float* ps = pose + (int64_t)i * 6;
-    Mix p;
-    mixture_of(o, p);
-    float a[kNComp], zt[kNComp][3], zw[kNComp][3];
-    float mx = -INFINITY;
-    for (int j = 0; j < kNComp; ++j) {
-      float lg = p.lw[j] - 3.0f * logf(2.0f * (float)M_PI);
-      for (int d = 0; d < 3; ++d) {
-        zt[j][d] = (ps[d] - p.mt[j][d]) / p.st[j][d];
-        zw[j][d] = (ps[3 + d] - p.mw[j][d]) / p.sw[j][d];
-        lg += -0.5f * (zt[j][d] * zt[j][d] + zw[j][d] * zw[j][d]) -
-              logf(p.st[j][d]) - logf(p.sw[j][d]);
-      }
-      a[j] = lg;
-      mx = fmaxf(mx, lg);
+// the sum over a 16-row block of a tile's column (double), to biasP
+__device__ __forceinline__ void put_bias(const TrainArgs& a, int off, int n,
+                                         const float (&v)[4], int lane) {
+  double s = ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
+  s += __shfl_xor(s, 16);
+  s += __shfl_xor(s, 32);
+  if (lane < 16) a.biasP[(int64_t)blockIdx.x * kNBias + off + n] = s;
+}
+
+// four rows (bf16) of a tile's column into row `col` of the transposed matrix
+__device__ __forceinline__ void put_act(const TrainArgs& a, int base, int col,
+                                        int row0, const unsigned short (&h)[4],
+                                        int lane) {
+  ushort4 p;
+  p.x = h[0];
+  p.y = h[1];
+  p.z = h[2];
+  p.w = h[3];
+  *reinterpret_cast<ushort4*>(act_of(a, base + col) + row0 +
+                              4 * (lane >> 4)) = p;
+}
+
+// Forward and backward pass of 16 rows of a minibatch by one workgroup: the
+// minibatch's rows drawn (row i of step s is training row philox(s, i) mod N,
+// with replacement) or taken in order, the three layers, the mixture's
+// likelihood gradient, and the two hidden layers' dZ.  Activations go from
+// layer to layer through LDS, pre-activations stay in their wavefront's
+// registers until the backward pass needs them; the bf16 activations and dZ
+// (transposed, as the weight gradients' MFMA operands) and the block's bias
+// and loss sums (double) are what leaves the block.  Rows past B are zero.
+// Bound by latency (512 rows: 32 workgroups, seven dependent stages, the
+// weights from L2): one launch of 19 us, where a gather, a forward kernel, a
+// likelihood kernel of one thread per row, two GEMMs and three column sums
+// took 150 us.
+__global__ __launch_bounds__(kFWaves * 64) void k_train_rows(TrainArgs a) {
+  __shared__ __align__(16) unsigned short S[2][kFRows][kFLd];
+  __shared__ __align__(16) unsigned short D[kFRows][kR3Ld + kPad];
+  __shared__ float O[kFRows][kNOut];
+  __shared__ float ps[kFRows][6];
+  __shared__ int64_t src[kFRows];
+  __shared__ double lred[2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row0 = blockIdx.x * kFRows, B = a.B;
+  const int c = lane & 15, n = wv * 16 + c;  // the wavefront's tile's column
+  const int kg = (lane >> 4) * 8;
+  if (tid < kFRows) {
+    const int m = row0 + tid;
+    int64_t j = m;
+    if (a.gather) {
+      const U4 o = philox4x32_10((uint32_t)m, (uint32_t)(a.step >> 32),
+                                 (uint32_t)a.step, kBatch, (uint32_t)a.seed,
+                                 (uint32_t)(a.seed >> 32));
+      j = (int64_t)((((uint64_t)o.x << 32) | o.y) % (uint64_t)a.N);
     }
-    float s = 0.f;
-    for (int j = 0; j < kNComp; ++j) s += expf(a[j] - mx);
-    const float ll = mx + logf(s);
-    li = -(double)ll;
-    float* d = dout + (int64_t)i * kNOut;
-    for (int j = 0; j < kNComp; ++j) {
-      const float r = expf(a[j] - ll);
-      const float pi = expf(p.lw[j]);
-      const float* oj = o + 13 * j;
-      float* dj = d + 13 * j;
-      dj[0] = -(r - pi) * inv_b;
-      for (int q = 0; q < 3; ++q) {
-        dj[1 + q] = -r * zt[j][q] / p.st[j][q] * inv_b;
-        const float th = tanhf(oj[4 + q]);
-        dj[4 + q] = -r * zw[j][q] / p.sw[j][q] * (float)M_PI *
-                    (1.f - th * th) * inv_b;
-        float sg = sigm(oj[7 + q]);
-        dj[7 + q] = -r * (zt[j][q] * zt[j][q] - 1.f) / p.st[j][q] *
-                    (kSt1 - kSt0) * sg * (1.f - sg) * inv_b;
-        sg = sigm(oj[10 + q]);
-        dj[10 + q] = -r * (zw[j][q] * zw[j][q] - 1.f) / p.sw[j][q] *
-                     (kSw1 - kSw0) * sg * (1.f - sg) * inv_b;
-      }
-    }
+    src[tid] = j;
   }
-  red[threadIdx.x] = li;
+  TileB<kT1Ld> w1;
+  TileB<kNHid> w2;
+  tile_load<kT1Ld>(a.WT + kTOff1 + (int64_t)n * kT1Ld + kg, w1);
+  tile_load<kNHid>(a.WT + kTOff2 + (int64_t)n * kT2Ld + kg, w2);
+  for (int e = tid; e < kFRows * (kR3Ld + kPad); e += kFWaves * 64)
+    D[e / (kR3Ld + kPad)][e % (kR3Ld + kPad)] = 0;
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
+  if (tid < kFRows * kNFeat) {
+    const int r = tid / kNFeat, k = tid - r * kNFeat;
+    const unsigned short v =
+        row0 + r < B ? bf16_bits(a.feats[src[r] * kNFeat + k])
+                     : (unsigned short)0;
+    S[0][r][k] = v;
+    act_of(a, kActF + k)[row0 + r] = v;
+  } else if (tid < kFRows * (kNFeat + 6)) {
+    const int e = tid - kFRows * kNFeat, r = e / 6, q = e - 6 * r;
+    ps[r][q] = row0 + r < B ? a.poses[src[r] * 6 + q] : 0.f;
   }
-  if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
+  __syncthreads();
+  float z1[4], z2[4];
+  unsigned short h[4];
+  {
+    const f32x4 v = tile_mul<kT1Ld, kNFeat, kFLd>(S[0], w1, lane);
+    const float b = a.P[kOffB1 + n];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = (lane >> 4) * 4 + q;
+      z1[q] = v[q] + b;
+      h[q] = bf16_bits(silu(z1[q]));
+      S[1][r][n] = h[q];
+      if (row0 + r >= B) h[q] = 0;
+    }
+    put_act(a, kActH1, n, row0, h, lane);
+  }
+  TileB<kNHid> w3;
+  if (wv < kT3Rows / 16)
+    tile_load<kNHid>(a.WT + kTOff3 + (int64_t)n * kT3Ld + kg, w3);
+  __syncthreads();
+  {
+    const f32x4 v = tile_mul<kNHid, kNHid, kFLd>(S[1], w2, lane);
+    const float b = a.P[kOffB2 + n];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = (lane >> 4) * 4 + q;
+      z2[q] = v[q] + b;
+      h[q] = bf16_bits(silu(z2[q]));
+      S[0][r][n] = h[q];
+      if (row0 + r >= B) h[q] = 0;
+    }
+    put_act(a, kActH2, n, row0, h, lane);
+  }
+  TileB<kR3Ld> r3;
+  tile_load<kR3Ld>(a.WT + kTOffR3 + (int64_t)n * kR3Ld + kg, r3);
+  __syncthreads();
+  if (wv < kT3Rows / 16) {
+    const f32x4 v = tile_mul<kNHid, kNHid, kFLd>(S[0], w3, lane);
+    if (n < kNOut) {
+      const float b = a.P[kOffB3 + n];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) O[(lane >> 4) * 4 + q][n] = v[q] + b;
+    }
+  }
+  TileB<kNHid> r2;
+  tile_load<kNHid>(a.WT + kTOffR2 + (int64_t)n * kNHid + kg, r2);
+  __syncthreads();
+  // negative log-likelihood and its gradient: component j of row r by thread
+  // 8 r + j; the sums over a row's components run in component order
+  if (tid < kFRows * kNComp) {
+    const int r = tid / kNComp, j = tid - r * kNComp;
+    const bool in = row0 + r < B;
+    float* o = &O[r][13 * j];
+    const float* pose = ps[r];
+    const int l0 = lane & ~(kNComp - 1);
+    auto row_lse = [&](float v) {  // log sum exp over the row's components
+      float mx = -INFINITY;
+#pragma unroll
+      for (int q = 0; q < kNComp; ++q) mx = fmaxf(mx, __shfl(v, l0 + q));
+      const float e = expf(v - mx);
+      float t = 0.f;
+#pragma unroll
+      for (int q = 0; q < kNComp; ++q) t += __shfl(e, l0 + q);
+      return mx + logf(t);
+    };
+    auto sub = [](float x, float y) {  // rounded by itself: no product fused
+#pragma clang fp contract(off)
+      return x - y;
+    };
+    const float lw = o[0] - row_lse(o[0]);
+    float mt[3], mw[3], st[3], sw[3], zt[3], zw[3], th[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      mt[d] = o[1 + d];
+      th[d] = tanhf(o[4 + d]);
+      mw[d] = (float)M_PI * th[d];
+      st[d] = kSt0 + (kSt1 - kSt0) * sigm(o[7 + d]);
+      sw[d] = kSw0 + (kSw1 - kSw0) * sigm(o[10 + d]);
+    }
+    // One difference of the 24 is a single rounding of t - pi tanh, the others
+    // of t - fl(pi tanh): a step's bits decide those of the steps after it
+    // (bf16 roundings flip), so the places of the roundings are fixed here.
+    const float last = fmaf(-(float)M_PI, th[2], pose[5]);
+    float lg = lw - 3.0f * logf(2.0f * (float)M_PI);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      zt[d] = (pose[d] - mt[d]) / st[d];
+      zw[d] = (j == kNComp - 1 && d == 2 ? last : sub(pose[3 + d], mw[d])) /
+              sw[d];
+      lg += -0.5f * (zt[d] * zt[d] + zw[d] * zw[d]) - logf(st[d]) -
+            logf(sw[d]);
+    }
+    const float ll = row_lse(lg);
+    const float rj = expf(lg - ll), pi = expf(lw);
+    float dj[13];
+    dj[0] = -(rj - pi) * a.inv_b;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      dj[1 + q] = -rj * zt[q] / st[q] * a.inv_b;
+      dj[4 + q] = -rj * zw[q] / sw[q] * (float)M_PI * fmaf(-th[q], th[q], 1.f) *
+                  a.inv_b;
+      float sg = sigm(o[7 + q]);
+      dj[7 + q] = -rj * fmaf(zt[q], zt[q], -1.f) / st[q] * (kSt1 - kSt0) * sg *
+                  (1.f - sg) * a.inv_b;
+      sg = sigm(o[10 + q]);
+      dj[10 + q] = -rj * fmaf(zw[q], zw[q], -1.f) / sw[q] * (kSw1 - kSw0) * sg *
+                   (1.f - sg) * a.inv_b;
+    }
+#pragma unroll
+    for (int q = 0; q < 13; ++q) {
+      o[q] = in ? dj[q] : 0.f;
+      D[r][13 * j + q] = in ? bf16_bits(dj[q]) : (unsigned short)0;
+    }
+    // eight rows a wavefront, one value each
+    const double l = wave_sum(j == 0 && in ? -(double)ll : 0.0);
+    if (lane == 0) lred[wv] = l;
+  }
+  __syncthreads();
+  if (tid == 0) a.lossP[blockIdx.x] = lred[0] + lred[1];
+  // dZ2 = (dout W3^T) silu'(Z2), dZ1 = (dZ2 W2^T) silu'(Z1)
+  {
+    const f32x4 v = tile_mul<kR3Ld, kR3Ld, kR3Ld + kPad>(D, r3, lane);
+    float dz[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      dz[q] = v[q] * dsilu(z2[q]);
+      h[q] = bf16_bits(dz[q]);
+      S[1][(lane >> 4) * 4 + q][n] = h[q];
+    }
+    put_act(a, kActZ2, n, row0, h, lane);
+    put_bias(a, kNHid, n, dz, lane);
+  }
+  __syncthreads();
+  {
+    const f32x4 v = tile_mul<kNHid, kNHid, kFLd>(S[1], r2, lane);
+    float dz[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      dz[q] = v[q] * dsilu(z1[q]);
+      h[q] = bf16_bits(dz[q]);
+    }
+    put_act(a, kActZ1, n, row0, h, lane);
+    put_bias(a, 0, n, dz, lane);
+  }
+  // the output layer's columns
+  if (tid < kNOut) {
+    double s = 0.0;
+    for (int r = 0; r < kFRows; ++r) s += (double)O[r][tid];
+    a.biasP[(int64_t)blockIdx.x * kNBias + 2 * kNHid + tid] = s;
+  }
+  for (int e = tid; e < kT3Rows * kFRows; e += kFWaves * 64) {
+    const int col = e / kFRows, r = e - col * kFRows;
+    act_of(a, kActD + col)[row0 + r] = D[r][col];
+  }
 }
 
-// Adam (Kingma & Ba) on fp32 master parameters
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ p,
-                                              const float* __restrict__ g,
-                                              float* __restrict__ m,
-                                              float* __restrict__ v, int n,
-                                              float lr, float b1, float b2,
-                                              float eps, float c1, float c2) {
+// One parameter's gradient: stored, or taken as an Adam step (Kingma & Ba) on
+// the fp32 master parameter
+__device__ __forceinline__ float take_grad(const AdamArgs& w, int i, float g) {
+  if (w.G) {
+    w.G[i] = g;
+    return 0.f;
+  }
+  const float mi = w.b1 * w.m[i] + (1.f - w.b1) * g;
+  const float vi = w.b2 * w.v[i] + (1.f - w.b2) * g * g;
+  w.m[i] = mi;
+  w.v[i] = vi;
+  const float p = w.P[i] - w.lr * (mi / w.c1) / (sqrtf(vi / w.c2) + w.eps);
+  w.P[i] = p;
+  return p;
+}
+// the updated weight (k, n) of matrix 1..3 in the bf16 copies
+__device__ __forceinline__ void put_weight(unsigned short* WT, int mat, int k,
+                                           int n, float p) {
+  const unsigned short h = bf16_bits(p);
+  if (mat == 1) {
+    WT[kTOff1 + n * kT1Ld + k] = h;
+  } else if (mat == 2) {
+    WT[kTOff2 + n * kT2Ld + k] = h;
+    WT[kTOffR2 + k * kNHid + n] = h;
+  } else {
+    WT[kTOff3 + n * kT3Ld + k] = h;
+    WT[kTOffR3 + k * kR3Ld + n] = h;
+  }
+}
+// the matrix, first row and first column of weight tile t (16 x 16)
+__device__ __forceinline__ int weight_tile(int t, int& k0, int& n0) {
+  constexpr int kHT = kNHid / 16, kOT = kT3Rows / 16;
+  if (t < kHT * kHT) {
+    k0 = t / kHT * 16;
+    n0 = t % kHT * 16;
+    return 2;
+  }
+  t -= kHT * kHT;
+  if (t < kHT * kOT) {
+    k0 = t / kOT * 16;
+    n0 = t % kOT * 16;
+    return 3;
+  }
+  k0 = 0;
+  n0 = (t - kHT * kOT) * 16;
+  return 1;
+}
+
+// Weight gradients H2^T dout, H1^T dZ2 and feats^T dZ1 (one wavefront per 16
+// x 16 tile, over the rows in order; both operands are 16-byte loads of the
+// transposed activations) with their Adam step or, for a split of many rows
+// (blockIdx.y), the split's partial gradient.  The blocks past the tiles sum
+// the biases' columns over the row blocks and, the last one, the loss (both
+// once, in double).  Bound by latency at a minibatch's size (16 chunks of 32
+// rows): 8.8 us with Adam, where three GEMMs whose 64 x 64 tiles left most of
+// the chip idle and an update pass took 113 us.
+constexpr int kTilesW = (kNHid / 16) * (kNHid / 16) +
+                        (kNHid / 16) * (kT3Rows / 16) + kNHid / 16;
+constexpr int kTileBlocks = kTilesW / 4;
+constexpr int kBiasBlocks = (kNBias + 63) / 64;
+static_assert(kTilesW % 4 == 0, "four tiles a block");
+__global__ __launch_bounds__(256) void k_train_weights(TrainArgs a, AdamArgs w,
+                                                       int n_split,
+                                                       float* split,
+                                                       double* loss) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if ((int)blockIdx.x >= kTileBlocks) {
+    if (blockIdx.y > 0) return;
+    __shared__ double part[256];
+    const int blk = blockIdx.x - kTileBlocks, nb = a.Bp / kFRows;
+    double s = 0.0;
+    if (blk < kBiasBlocks) {
+      const int c = 64 * blk + lane;
+      if (c < kNBias)
+#pragma unroll 8
+        for (int q = wv; q < nb; q += 4) s += a.biasP[(int64_t)q * kNBias + c];
+      part[tid] = s;
+      __syncthreads();
+      if (wv == 0 && c < kNBias) {
+        const float g = (float)(((part[lane] + part[64 + lane]) +
+                                 part[128 + lane]) + part[192 + lane]);
+        const int i = c < kNHid       ? kOffB1 + c
+                      : c < 2 * kNHid ? kOffB2 + c - kNHid
+                                      : kOffB3 + c - 2 * kNHid;
+        take_grad(w, i, g);
+      }
+    } else {
+      for (int q = tid; q < nb; q += 256) s += a.lossP[q];
+      part[tid] = s;
+      __syncthreads();
+      for (int st = 128; st > 0; st >>= 1) {
+        if (tid < st) part[tid] += part[tid + st];
+        __syncthreads();
+      }
+      if (tid == 0) *loss = part[0];
+    }
+    return;
+  }
+  int k0, n0;
+  const int mat = weight_tile(blockIdx.x * 4 + wv, k0, n0);
+  const unsigned short* A =
+      act_of(a, (mat == 1 ? kActF : mat == 2 ? kActH1 : kActH2) + k0 +
+                    (lane & 15)) + (lane >> 4) * 8;
+  const unsigned short* Bt =
+      act_of(a, (mat == 1 ? kActZ1 : mat == 2 ? kActZ2 : kActD) + n0 +
+                    (lane & 15)) + (lane >> 4) * 8;
+  const int steps = a.Bp / kKStep;
+  const int s0 = (int)((int64_t)steps * blockIdx.y / n_split);
+  const int s1 = (int)((int64_t)steps * (blockIdx.y + 1) / n_split);
+  typedef const bf16x8 __attribute__((address_space(1))) gbf;
+  f32x4 acc{0.f, 0.f, 0.f, 0.f};
+  int q = s0;
+  auto chunks = [&](auto len) {  // len chunks at a time: loads, then products
+    constexpr int kL = decltype(len)::value;
+    for (; q + kL <= s1; q += kL) {
+      bf16x8 x[kL], y[kL];
+#pragma unroll
+      for (int e = 0; e < kL; ++e) {
+        x[e] = *(gbf*)(A + (int64_t)kKStep * (q + e));
+        y[e] = *(gbf*)(Bt + (int64_t)kKStep * (q + e));
+      }
+#pragma unroll
+      for (int e = 0; e < kL; ++e)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[e], y[e], acc, 0, 0,
+                                                      0);
+    }
+  };
+  chunks(std::integral_constant<int, 16>{});
+  chunks(std::integral_constant<int, 4>{});
+  chunks(std::integral_constant<int, 1>{});
+  const int nout = mat == 3 ? kNOut : kNHid;
+  const int off = mat == 1 ? kOffW1 : mat == 2 ? kOffW2 : kOffW3;
+  const int n = n0 + (lane & 15);
+  if (n >= nout) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int k = k0 + 4 * (lane >> 4) + e, i = off + k * nout + n;
+    if (n_split > 1) {
+      split[(int64_t)blockIdx.y * kNParams + i] = acc[e];
+    } else {
+      const float p = take_grad(w, i, acc[e]);
+      if (!w.G) put_weight(a.WT, mat, k, n, p);
+    }
+  }
+}
+
+// the splits' weight gradients summed (double, in order), with their Adam step
+__global__ __launch_bounds__(256) void k_train_splits(
+    AdamArgs w, unsigned short* WT, const float* __restrict__ split,
+    int n_split) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  if (i >= kNParams) return;
+  int mat, k, n;
+  if (i < kOffB1) {
+    mat = 1; k = i / kNHid; n = i % kNHid;
+  } else if (i >= kOffW2 && i < kOffB2) {
+    mat = 2; k = (i - kOffW2) / kNHid; n = (i - kOffW2) % kNHid;
+  } else if (i >= kOffW3 && i < kOffB3) {
+    mat = 3; k = (i - kOffW3) / kNOut; n = (i - kOffW3) % kNOut;
+  } else {
+    return;  // a bias
+  }
+  double s = 0.0;
+  for (int q = 0; q < n_split; ++q) s += (double)split[(int64_t)q * kNParams + i];
+  const float p = take_grad(w, i, (float)s);
+  if (!w.G) put_weight(WT, mat, k, n, p);
 }
 
 // ----------------------------------------------------------------------------
@@ -933,19 +1128,31 @@ __global__ __launch_bounds__(W * kWave) void k_pose_move(
 // ----------------------------------------------------------------------------
 // launchers
 // ----------------------------------------------------------------------------
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
-  if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  dim3 grid((a.N + kTile - 1) / kTile, (a.M + kTile - 1) / kTile);
-  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, a);
+hipError_t launch_mlp_forward(const float* P, const unsigned short* WT,
+                              const float* X, int B, float* out,
+                              hipStream_t st) {
+  if (B <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_mlp_forward, dim3((B + kFRows - 1) / kFRows),
+                     dim3(kFWaves * 64), 0, st, P, WT, X, B, out);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_forward(const float* P, const float* X, int B,
-                              float* Z1, float* H1, float* Z2, float* H2,
-                              float* out, hipStream_t st) {
-  if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mlp_forward, dim3((B + kFRows - 1) / kFRows),
-                     dim3(kFWaves * 64), 0, st, P, X, B, Z1, H1, Z2, H2, out);
+// one split per 4096 rows (64 at most): up to there a wavefront per tile
+// takes all rows, 128 chunks, in order
+int train_splits(int Bp) { return std::min(64, (Bp + 4095) / 4096); }
+
+hipError_t launch_train_step(const TrainArgs& a, const AdamArgs& w,
+                             float* split, double* loss, hipStream_t st) {
+  if (a.B <= 0 || a.Bp % kKStep != 0 || a.Bp < a.B) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_train_rows, dim3(a.Bp / kFRows), dim3(kFWaves * 64), 0,
+                     st, a);
+  const int ns = train_splits(a.Bp);
+  hipLaunchKernelGGL(k_train_weights,
+                     dim3(kTileBlocks + kBiasBlocks + 1, ns), dim3(256), 0, st,
+                     a, w, ns, split, loss);
+  if (ns > 1)
+    hipLaunchKernelGGL(k_train_splits, dim3((kNParams + 255) / 256), dim3(256),
+                       0, st, w, a.WT, split, ns);
   return hipGetLastError();
 }
 
@@ -966,28 +1173,6 @@ hipError_t launch_weights_bf16(const float* P, unsigned short* WT,
                                hipStream_t st) {
   hipLaunchKernelGGL(k_weights_bf16, dim3((kTSize + 255) / 256), dim3(256), 0,
                      st, P, WT);
-  return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float* X, int rows, int cols, int64_t ld,
-                         float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_colsum, dim3((cols + 63) / 64), dim3(256), 0, st, X,
-                     rows, cols, ld, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_nll(const float* out, const float* pose, int B,
-                      float* dout, double* loss_part, hipStream_t st) {
-  hipLaunchKernelGGL(k_nll, dim3((B + 255) / 256), dim3(256), 0, st, out,
-                     pose, B, 1.0f / (float)B, dout, loss_part);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n,
-                       float lr, float b1, float b2, float eps, float c1,
-                       float c2, hipStream_t st) {
-  hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, st, p, g, m,
-                     v, n, lr, b1, b2, eps, c1, c2);
   return hipGetLastError();
 }
 
@@ -1029,34 +1214,4 @@ hipError_t launch_pose_move(const GridDev& g, const LigDev* ligs,
   return hipGetLastError();
 }
 
-}  // namespace bpmf
-
-namespace bpmf {
-namespace {
-// minibatch gather: row i of step s is row philox(s, i) mod N (sampling with
-// replacement)
-__global__ __launch_bounds__(256) void k_gather(
-    const float* __restrict__ feats, const float* __restrict__ poses,
-    int64_t N, int B, uint64_t seed, uint64_t step, float* __restrict__ bf,
-    float* __restrict__ bp) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B) return;
-  const U4 o = philox4x32_10((uint32_t)i, (uint32_t)(step >> 32),
-                             (uint32_t)step, kBatch, (uint32_t)seed,
-                             (uint32_t)(seed >> 32));
-  const uint64_t r = ((uint64_t)o.x << 32) | o.y;
-  const int64_t j = (int64_t)(r % (uint64_t)N);
-  for (int q = 0; q < kNFeat; ++q) bf[(int64_t)i * kNFeat + q] = feats[j * kNFeat + q];
-  for (int q = 0; q < 6; ++q) bp[(int64_t)i * 6 + q] = poses[j * 6 + q];
-}
-}  // namespace
-
-hipError_t launch_gather_batch(const float* feats, const float* poses,
-                               int64_t N, int B, uint64_t seed,
-                               uint64_t step, float* bf, float* bp,
-                               hipStream_t st) {
-  hipLaunchKernelGGL(k_gather, dim3((B + 255) / 256), dim3(256), 0, st, feats,
-                     poses, N, B, seed, step, bf, bp);
-  return hipGetLastError();
-}
 }  // namespace bpmf

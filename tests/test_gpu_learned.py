@@ -120,6 +120,62 @@ def test_gradients_match_oracle():
     ctx.close()
 
 
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 32, 33, 4096, 4097])
+def test_training_row_and_split_edges(B):
+    """Batches around the 16-row blocks, the 32-row chunks and the first split
+    of the weight gradients: the gradient against the oracle (tolerances of
+    this file), one Adam step on B copies of a row against that gradient (the
+    update to 1e-4 of lr and two ulp of the parameter: fp32 moments and bias
+    corrections), and the weight copies it leaves against fresh ones."""
+    print_case(f"mlp training edges B={B}")
+    rng, system, lig, p, ctx, lid, _ = _setup(7)
+    f = rng.uniform(-1, 1, (B, 16)).astype(np.float32)
+    poses = np.concatenate([rng.normal(scale=1.0, size=(B, 3)),
+                            rng.normal(scale=0.8, size=(B, 3))],
+                           1).astype(np.float32)
+    g, loss = ctx.proposal_grad(lid, dev(f, torch.float32),
+                                dev(poses, torch.float32))
+    g = unflat(g.cpu().numpy())
+    pb = {k: bf16(v) for k, v in p.items()}
+    loss64, g64, _ = Lr.nll_grad(pb, f.astype(np.float64),
+                                 poses[:, :3].astype(np.float64),
+                                 poses[:, 3:].astype(np.float64))
+    assert abs(loss - loss64) < 1e-2 * abs(loss64)
+    for k in g64:
+        a, b = g[k].ravel(), g64[k].ravel()
+        assert rel_l2(a, b) < 2e-2, (k, rel_l2(a, b))
+        assert cosine(a, b) > 0.999, (k, cosine(a, b))
+    f[:], poses[:] = f[0], poses[0]
+    g, loss = ctx.proposal_grad(lid, dev(f, torch.float32),
+                                dev(poses, torch.float32))
+    g = g.cpu().numpy().astype(np.float64)
+    p0 = np.asarray(ctx.proposal_params(lid), np.float64)
+    lr = 1e-2
+    step = ctx.proposal_train(lid, dev(f[:1], torch.float32),
+                              dev(poses[:1], torch.float32), batch=B, steps=1,
+                              lr=lr, losses=True)
+    assert abs(step[0] - loss) <= 1e-12 * abs(loss)
+    p1 = ctx.proposal_params(lid)
+    c1 = float(np.float32(1) - np.float32(0.9))
+    c2 = float(np.float32(1) - np.float32(0.999))
+    want = p0 - lr * (0.1 * g / c1) / (np.sqrt(0.001 * g * g / c2) + 1e-8)
+    tol = 1e-4 * lr + 2 * np.spacing(np.abs(p1)).astype(np.float64)
+    assert np.all(np.abs(p1 - want) <= tol), np.abs(p1 - want).max()
+    rows = dev(rng.uniform(-1, 1, (33, 16)), torch.float32)
+    kept = ctx.proposal_forward(lid, rows).cpu().numpy()
+    ctx.proposal_params(lid, new=p1)
+    assert np.array_equal(kept, ctx.proposal_forward(lid, rows).cpu().numpy())
+    kept, _ = ctx.proposal_grad(lid, dev(f, torch.float32),
+                                dev(poses, torch.float32))
+    ctx.proposal_train(lid, dev(f[:1], torch.float32),
+                       dev(poses[:1], torch.float32), batch=B, steps=2, lr=lr)
+    ctx.proposal_params(lid, new=p1)
+    again, _ = ctx.proposal_grad(lid, dev(f, torch.float32),
+                                 dev(poses, torch.float32))
+    assert torch.equal(kept, again)
+    ctx.close()
+
+
 @pytest.mark.parametrize("which", ["c1", "wide90", "wide100"])
 def test_pose_features_match_oracle(which):
     print_case("pose features", which)
