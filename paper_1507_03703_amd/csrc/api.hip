@@ -2459,8 +2459,9 @@ extern "C" int bpmf_pose_features(bpmf_ctx* c, int lid, const float* dev_x,
   if (N == 0) return BPMF_OK;
   if (!dev_x || !dev_feats || !dev_poses)
     return fail(BPMF_E_INVAL, "null pose_features argument");
-  HIP_TRY(launch_pose_features(c->d_ligs + lid, c->ligs[lid].d_prop, dev_x, N,
-                               dev_feats, dev_poses, c->stream));
+  HIP_TRY(launch_pose_features(c->d_ligs + lid, c->ligs[lid].d_prop,
+                               c->ligs[lid].dev.n, dev_x, N, dev_feats, dev_poses,
+                               c->stream));
   return BPMF_OK;
 }
 

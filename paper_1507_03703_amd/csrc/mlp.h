@@ -105,7 +105,8 @@ hipError_t launch_mlp_forward(const float* P, const unsigned short* WT,
 int train_splits(int Bp);
 hipError_t launch_train_step(const TrainArgs& a, const AdamArgs& w,
                              float* split, double* loss, hipStream_t st);
-hipError_t launch_pose_features(const LigDev* lig, const PropDev* prop,
+// n: the ligand's atoms
+hipError_t launch_pose_features(const LigDev* lig, const PropDev* prop, int n,
                                 const float* xs, int64_t N, float* feats,
                                 float* poses, hipStream_t st);
 // the network on the current configurations of tasks [row0, row0 + rows)

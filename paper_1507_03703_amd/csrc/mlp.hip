@@ -778,46 +778,128 @@ __device__ float dihedral_angle(const float* x, int4 q) {
   return atan2f(y, xx);
 }
 
-// pose (t, omega) and features of one configuration x of ligand L
-__device__ void pose_features_one(const LigDev& L, const PropDev& P,
-                                  const float* x, float* po, float* fo) {
-  const int n = L.n;
+// the translation of the pose of configuration x of ligand L, and the rotation
+__device__ void pose_translation(const LigDev& L, const float* x, float* t) {
   double c[3] = {0, 0, 0}, M = 0;
-  for (int a = 0; a < n; ++a) {
+  for (int a = 0; a < L.n; ++a) {
     const double m = L.mass[a];
     M += m;
     for (int d = 0; d < 3; ++d) c[d] += m * x[3 * a + d];
   }
+  for (int d = 0; d < 3; ++d) t[d] = (float)(c[d] / M - L.site[d]);
+}
+__device__ void pose_rotation(const PropDev& P, const float* x, float* om) {
   Frame F;
   body_frame(x, P.frame, F);
   double R[3][3], w[3];
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) R[a][b] = F.R[a][b];
   log_rot(R, w);
-  for (int d = 0; d < 3; ++d) {
-    po[d] = (float)(c[d] / M - L.site[d]);
-    po[3 + d] = (float)w[d];
+  for (int d = 0; d < 3; ++d) om[d] = (float)w[d];
+}
+
+// m rows of `len` floats between consecutive memory g and LDS rows `row`
+// floats apart, by the whole
+// workgroup; 16 bytes at a time where g is aligned
+constexpr int kFeatWaves = 4;
+template <bool OUT>
+__device__ __forceinline__ void move_rows(float* g, int len, int m, float* l,
+                                          int row) {
+  const int tid = threadIdx.x, total = m * len;
+  const int quads = (reinterpret_cast<uintptr_t>(g) & 15) == 0 ? total / 4 : 0;
+#pragma unroll 4
+  for (int q = tid; q < quads; q += kFeatWaves * 64) {
+    float4* g4 = reinterpret_cast<float4*>(g) + q;
+    float v[4] = {};
+    if (!OUT) *reinterpret_cast<float4*>(v) = *g4;
+    int c = 4 * q % len;
+    float* at = l + 4 * q / len * row + c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (OUT)
+        v[e] = *at;
+      else
+        *at = v[e];
+      ++at;
+      if (++c == len) {
+        c = 0;
+        at += row - len;
+      }
+    }
+    if (OUT) *g4 = make_float4(v[0], v[1], v[2], v[3]);
   }
-  for (int q = 0; q < kNFeat; ++q) fo[q] = 0.f;
-  for (int q = 0; q < P.n_cond; ++q) {
-    const float phi = dihedral_angle(x, P.cond[q]);
-    float s, cs;
-    sincosf(phi, &s, &cs);
-    fo[2 * q] = s;
-    fo[2 * q + 1] = cs;
+  for (int e = 4 * quads + tid; e < total; e += kFeatWaves * 64) {
+    float* at = l + e / len * row + e % len;
+    if (OUT)
+      g[e] = *at;
+    else
+      *at = g[e];
   }
 }
 
-// one thread per configuration xs[i] of one ligand
-__global__ __launch_bounds__(128) void k_pose_features(
+// 64 configurations xs[i] of one ligand by four wavefronts: one takes the
+// centres of mass, one the rotations, two the torsions, since 100000
+// configurations are one and a half wavefronts per SIMD and the serial chain
+// of a configuration (sums, atan2, a rotation's logarithm) was what bound
+// this.  Positions and results pass through LDS, so that memory is read and
+// written 16 bytes at a time; an odd row length spreads the rows over the
+// banks.  100000 configurations of 24 atoms: 12 us; one thread for all of
+// a configuration took 33 us (42 us staged like this).  64 rows of a large
+// ligand would pass 64 KB: 32 then.
+constexpr int kFeatOut = 6 + kNFeat;
+__host__ __device__ constexpr int feat_row(int n) {
+  return (3 * n > kFeatOut ? 3 * n : kFeatOut) | 1;
+}
+__host__ __device__ constexpr int feat_confs(int n) {
+  return feat_row(n) <= 256 ? 64 : 32;
+}
+__global__ __launch_bounds__(kFeatWaves * 64) void k_pose_features(
     const LigDev* __restrict__ lig, const PropDev* __restrict__ prop,
     const float* __restrict__ xs, int64_t N, float* __restrict__ feats,
     float* __restrict__ poses) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
+  extern __shared__ float s_conf[];
   const LigDev& L = *lig;
-  pose_features_one(L, *prop, xs + i * L.n * 3, poses + i * 6,
-                    feats + i * kNFeat);
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int len = 3 * L.n, row = feat_row(L.n), most = feat_confs(L.n);
+  const int64_t i0 = (int64_t)blockIdx.x * most;
+  const int m = (int)(N - i0 < most ? N - i0 : most);
+  move_rows<false>(const_cast<float*>(xs) + i0 * len, len, m, s_conf, row);
+  __syncthreads();
+  float* x = s_conf + lane * row;
+  float v[kNFeat / 2];
+  if (lane < m) {
+    if (wv == 0) {
+      pose_translation(L, x, v);
+    } else if (wv == 1) {
+      pose_rotation(*prop, x, v);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kNFeat / 4; ++q) {
+        const int k = (wv - 2) + 2 * q;  // torsion
+        v[2 * q] = v[2 * q + 1] = 0.f;
+        if (k < prop->n_cond)
+          sincosf(dihedral_angle(x, prop->cond[k]), &v[2 * q], &v[2 * q + 1]);
+      }
+    }
+  }
+  __syncthreads();
+  if (lane < m) {
+    if (wv < 2) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) x[3 * wv + d] = v[d];
+    } else {
+#pragma unroll
+      for (int q = 0; q < kNFeat / 4; ++q) {
+        const int k = (wv - 2) + 2 * q;
+        x[6 + 2 * k] = v[2 * q];
+        x[7 + 2 * k] = v[2 * q + 1];
+      }
+    }
+  }
+  __syncthreads();
+  move_rows<true>(poses + i0 * 6, 6, m, s_conf, row);
+  move_rows<true>(feats + i0 * kNFeat, kNFeat, m, s_conf + 6, row);
 }
 
 // wavefront maximum of a double (DPP tree as in wave_sum)
@@ -1176,15 +1258,16 @@ hipError_t launch_weights_bf16(const float* P, unsigned short* WT,
   return hipGetLastError();
 }
 
-hipError_t launch_pose_features(const LigDev* lig, const PropDev* prop,
+hipError_t launch_pose_features(const LigDev* lig, const PropDev* prop, int n,
                                 const float* xs, int64_t N, float* feats,
                                 float* poses, hipStream_t st) {
   if (N <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pose_features, dim3((unsigned)((N + 127) / 128)),
-                     dim3(128), 0, st, lig, prop, xs, N, feats, poses);
+  const int m = feat_confs(n);
+  hipLaunchKernelGGL(k_pose_features, dim3((unsigned)((N + m - 1) / m)),
+                     dim3(kFeatWaves * 64), m * feat_row(n) * 4, st, lig, prop,
+                     xs, N, feats, poses);
   return hipGetLastError();
 }
-
 
 hipError_t launch_pose_move(const GridDev& g, const LigDev* ligs,
                             const PropDev* props, const PoseTask* tasks,

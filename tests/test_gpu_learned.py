@@ -203,6 +203,30 @@ def test_pose_features_match_oracle(which):
     ctx.close()
 
 
+@pytest.mark.parametrize("which,N", [("c1", 1), ("c1", 63), ("c1", 65),
+                                     ("wide90", 31), ("wide90", 33)])
+def test_pose_features_block_edges(which, N):
+    """Numbers of configurations around a block's 64 (32 for a large ligand),
+    at a 16-byte address and past one: each configuration's results are those
+    of the configuration alone, bit for bit, and nothing else is written."""
+    print_case(f"pose features edges {which} {N}")
+    rng, system, lig, p, ctx, lid, cond = _setup(3, which)
+    n = len(lig.mass)
+    xs = (lig.x0[0] + rng.normal(scale=0.2, size=(N, n, 3)))
+    flat_x = dev(np.concatenate([np.zeros(1), xs.ravel()]), torch.float32)
+    x = flat_x.clone()[1:].view(N, n, 3)   # four bytes past an aligned address
+    assert x.data_ptr() % 16 == 4
+    f, po = ctx.pose_features(lid, x)
+    fa, pa = ctx.pose_features(lid, x.clone())
+    assert torch.equal(f, fa) and torch.equal(po, pa)
+    for i in {0, N // 2, N - 1}:
+        f1, p1 = ctx.pose_features(lid, x[i:i + 1].clone())
+        assert torch.equal(f1[0], f[i]) and torch.equal(p1[0], po[i])
+        want = Lr.features(xs[i].astype(np.float32).astype(np.float64), cond)
+        assert np.allclose(f[i].cpu().numpy(), want, atol=2e-5)
+    ctx.close()
+
+
 def _check_pose_moves(ctx, og, lig, lid, seed, rounds, sweeps=2):
     """`rounds` times: a few sweeps of every ligand, then one pose move of
     every ligand with a proposal (ligand -1), checked replica by replica on
