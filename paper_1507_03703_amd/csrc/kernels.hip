@@ -924,20 +924,218 @@ __global__ __launch_bounds__(W * kWave) void k_energy_matrix(
   }
 }
 
-// The same u_kn with one wavefront per sample and no workgroup barrier
-// inside a sample: for ligands whose pair terms are not in the energy.  A
-// block of kUknWaves wavefronts stages the topology of its current job once
-// (shared by its wavefronts); the job's samples are dealt to the wavefronts
-// in groups of kUknWaveGroup consecutive ones.  A wavefront evaluates a
-// sample alone: lane l owns atoms l and l + 64 (AP = 2) or l; the grid terms
-// of its atoms, every bonded chunk of the ligand (energies only), the
-// mass-weighted position sums of the restraint, then double sums over the
-// wavefront, as the lean block evaluation forms them: U0 = (bonded total) +
-// U_I, and the C channel sums.  Its LDS (positions, the group's columns) is
-// its own; LDS operations of one wavefront complete in order, so its lanes
-// see each other's stores after a wavefront-scope fence.
+// The same u_kn with one wavefront per sample, or one for two samples at
+// once (H = 2), and no workgroup barrier inside a sample: for ligands whose
+// pair terms are not in the energy.  A block of kUknWaves wavefronts stages
+// the topology of its current job once (shared by its wavefronts); the job's
+// samples are dealt to the wavefronts in runs, worked through in groups of
+// up to kUknWaveGroup.  A wavefront evaluates a sample alone: lane l owns atoms l and l + 64
+// (AP = 2) or l; the grid terms of its atoms, every bonded chunk of the ligand
+// (energies only), the mass-weighted position sums of the restraint, then
+// double sums over the wavefront, as the lean block evaluation forms them:
+// U0 = (bonded total) + U_I, and the C channel sums.  Its LDS (positions, the
+// group's columns) is its own; LDS operations of one wavefront complete in
+// order, so its lanes see each other's stores after a wavefront-scope fence.
+//
+// Bound by instruction issue (some 600 vector instructions a sample whatever
+// part of the lanes owns an atom), so up to 32 atoms the wavefront's halves
+// take a sample each: 225000 poses of 24 atoms, 50 states and 5 channels take
+// 212 us, one at a time 289 us.  A wavefront's share is a run of whole pairs:
+// dealt in groups of 8, 133 samples to four wavefronts left one with 40 (32
+// ligands of 10 to 80 atoms, 3200 samples each: 165 -> 135 us, with the
+// halves).  Registers: four wavefronts a SIMD with 3 channels, three with 5
+// (four spill: 230 us instead of 212).
+// The float sums of a half are those of a whole wavefront with the sample in
+// its lower half: a lane's bonded items 64 apart in one accumulator, the
+// position sums over two rows of 16.
+
+// sum over each half of the wavefront, to all its lanes
+__device__ __forceinline__ double half_sum(double v) {
+  v += dpp_d<0xB1, 0xf>(v);
+  v += dpp_d<0x4E, 0xf>(v);
+  v += dpp_d<0x141, 0xf>(v);
+  v += dpp_d<0x140, 0xf>(v);
+  const long long b = __double_as_longlong(v);
+  const auto lo = __builtin_amdgcn_permlane16_swap((int)(b & 0xffffffffll),
+                                                   (int)(b & 0xffffffffll),
+                                                   false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((int)(b >> 32),
+                                                   (int)(b >> 32), false,
+                                                   false);
+  return __longlong_as_double(((long long)hi[0] << 32) |
+                              (long long)(unsigned)lo[0]) +
+         __longlong_as_double(((long long)hi[1] << 32) |
+                              (long long)(unsigned)lo[1]);
+}
+__device__ __forceinline__ float half_sumf(float v) {
+  v += dpp_f<0xB1, 0xf>(v);
+  v += dpp_f<0x4E, 0xf>(v);
+  v += dpp_f<0x141, 0xf>(v);
+  v += dpp_f<0x140, 0xf>(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(v),
+                                                  __float_as_int(v), false,
+                                                  false);
+  return __int_as_float(r[0]) + __int_as_float(r[1]);
+}
+
+// The columns of samples q0 .. q1 - 1 (at most kUknWaveGroup) of job J, by one
+// wavefront.
+template <int C, int AP, int H>
+__device__ __forceinline__ void ukn_group(const GridDev& g, const LigDev& L,
+                                          const UknJob& J, const Shared& sh,
+                                          const double* ew, float4* pos,
+                                          double* col, const float (&m)[AP],
+                                          const float (&sc)[AP][C],
+                                          const bool (&own)[AP], int64_t q0,
+                                          int64_t q1, int lane) {
+  static_assert(H == 1 || AP == 1, "two samples at once: up to 32 atoms");
+  typedef const float __attribute__((address_space(1))) gfloat;
+  constexpr int kSpan = kWave / H;
+  auto wave_fence = []() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  const Slots no_forces{nullptr, 0};
+  const int n = L.n, K = L.K;
+  const int hl = lane & (kSpan - 1), half = H == 2 ? lane >> 5 : 0;
+  if (H == 2) pos += kSpan * half;
+  const int ntc = (L.nt + kSpan - 1) / kSpan;
+  const int nac = (L.na + kSpan - 1) / kSpan;
+  const int nbc = (L.nb + kSpan - 1) / kSpan;
+  for (int64_t q = q0; q < q1; q += H) {
+    // the last sample again where the second half has none
+    const int64_t qs = H == 2 && q + half >= q1 ? q : q + half;
+    const gfloat* xq = (const gfloat*)J.xs + (size_t)(qs - J.first) * n * 3;
+    float x[AP][3];
+#pragma unroll
+    for (int a = 0; a < AP; ++a)
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        x[a][d] = own[a] ? xq[(hl + kWave * a) * 3 + d] : 0.f;
+#pragma unroll
+    for (int a = 0; a < AP; ++a)
+      if (own[a])
+        pos[hl + kWave * a] = make_float4(x[a][0], x[a][1], x[a][2], m[a]);
+    // the first atom's cell records load during the torsions, the second's
+    // (AP = 2) during the angles and bonds: one record set in registers at a
+    // time
+    float psi[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) psi[c] = 0.f;
+    Corners<C> cn;
+    if (own[0]) grid_fetch<C>(g, x[0][0], x[0][1], x[0][2], cn);
+    wave_fence();
+    // bonded terms, energies only, every chunk of the ligand
+    float eb[H] = {}, ea[H] = {}, et[H] = {};
+    // (the two accumulators of H = 2 change places from chunk to chunk)
+    auto chunks = [&](int nch, int items, float (&e)[H], auto term) {
+#pragma unroll 1
+      for (int ch = 0; ch < nch; ++ch) {
+        const int t = ch * kSpan + hl;
+        if (t < items) e[0] += term(t);
+        if (H == 2) {
+          const float first = e[0];
+          e[0] = e[H - 1];
+          e[H - 1] = first;
+        }
+      }
+    };
+    chunks(ntc, L.nt, et, [&](int t) {
+      return torsion_term<false>(pos, sh.tijkl[t], sh.tpar[t], no_forces);
+    });
+    auto angles_bonds = [&]() {
+      chunks(nac, L.na, ea, [&](int t) {
+        return angle_term<false>(pos, sh.aijk[t], sh.apar[t], no_forces);
+      });
+      chunks(nbc, L.nb, eb, [&](int t) {
+        return bond_term<false>(pos, sh.bij[t], sh.bpar[t], no_forces);
+      });
+    };
+#pragma unroll
+    for (int a = 0; a < AP; ++a) {
+      if (own[a]) {
+        float ev[C], dv[C][3];
+        grid_finish<C, false>(g, cn, sc[a], ev, dv);
+#pragma unroll
+        for (int c = 0; c < C; ++c) psi[c] += ev[c];
+      }
+      if (a + 1 < AP && own[a + 1])
+        grid_fetch<C>(g, x[a + 1][0], x[a + 1][1], x[a + 1][2], cn);
+      if (a + 1 < AP) angles_bonds();
+    }
+    if (AP == 1) angles_bonds();
+    // the centre of mass
+    float px = 0.f, py = 0.f, pz = 0.f;
+#pragma unroll
+    for (int a = 0; a < AP; ++a) {
+      px += m[a] * x[a][0];
+      py += m[a] * x[a][1];
+      pz += m[a] * x[a][2];
+    }
+    double U0b = (double)eb[0] + (double)ea[0] + (double)et[0];
+    if (H == 2) U0b += (double)eb[H - 1] + (double)ea[H - 1] + (double)et[H - 1];
+    double ps[C];
+    if (H == 2) {
+      px = half_sumf(px);
+      py = half_sumf(py);
+      pz = half_sumf(pz);
+      U0b = half_sum(U0b);
+#pragma unroll
+      for (int c = 0; c < C; ++c) ps[c] = half_sum((double)psi[c]);
+    } else {
+      wave_sumf3(px, py, pz);
+      U0b = wave_sum(U0b);
+#pragma unroll
+      for (int c = 0; c < C; ++c) ps[c] = wave_sum((double)psi[c]);
+    }
+    const float cx = px * L.inv_total_mass - L.site[0];
+    const float cy = py * L.inv_total_mass - L.site[1];
+    const float cz = pz * L.inv_total_mass - L.site[2];
+    const float d = sqrtf(cx * cx + cy * cy + cz * cz);
+    const float excess = d - L.d0;
+    const double ui = excess > 0.f
+                          ? 0.5 * (double)L.krest * (double)excess *
+                                (double)excess
+                          : 0.0;
+    const double U0 = U0b + 0.0 + 0.0 + ui;
+    // (a second half without a sample writes the first's column again)
+    double* cs = col + (qs - q0) * K;
+#pragma unroll 1
+    for (int k = hl; k < K; k += kSpan) {
+      double E = U0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) E = fma(ew[k * C + c], ps[c], E);
+      cs[k] = ew[K * C + k] * E;
+    }
+    // the next sample's position stores come after every lane's reads of
+    // this one
+    wave_fence();
+  }
+  // the group's columns, row by row: a run of consecutive samples of each row
+  // by consecutive lanes
+  wave_fence();
+  const int cnt = (int)(q1 - q0);
+  const int64_t n0 = q0 - J.first;
+  auto out = BPMF_GMEM(double, J.ukn);
+  if (cnt == kUknWaveGroup) {
+#pragma unroll 2
+    for (int i = lane; i < kUknWaveGroup * K; i += kWave) {
+      const int k = i / kUknWaveGroup, qq = i % kUknWaveGroup;
+      out[(size_t)k * J.ld + n0 + qq] = col[qq * K + k];
+    }
+  } else {
+#pragma unroll 1
+    for (int i = lane; i < cnt * K; i += kWave) {
+      const int k = i / cnt, qq = i - k * cnt;
+      out[(size_t)k * J.ld + n0 + qq] = col[qq * K + k];
+    }
+  }
+  wave_fence();
+}
+
 template <int C, int AP>
-__global__ __launch_bounds__(kUknWaves * kWave) void k_energy_matrix_wave(
+__global__ __launch_bounds__(kUknWaves * kWave, C == 3 ? 4 : 3) void k_energy_matrix_wave(
     GridDev g, const LigDev* __restrict__ ligs,
     const UknJob* __restrict__ jobs, int n_jobs, int64_t total) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -949,12 +1147,6 @@ __global__ __launch_bounds__(kUknWaves * kWave) void k_energy_matrix_wave(
   if (b0 >= b1) return;
   typedef const float __attribute__((address_space(1))) gfloat;
   typedef const double __attribute__((address_space(1))) gcdouble;
-  auto wave_fence = []() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
-  const Slots no_forces{nullptr, 0};
   for (int64_t s = b0; s < b1; ++j) {
     const UknJob J = jobs[j];
     const int64_t e = jobs[j + 1].first < b1 ? jobs[j + 1].first : b1;
@@ -975,133 +1167,33 @@ __global__ __launch_bounds__(kUknWaves * kWave) void k_energy_matrix_wave(
       ew[i] = i < K * C ? ((gcdouble*)L.wd)[i]
                         : ((gcdouble*)L.beta)[i - K * C];
     __syncthreads();
-    const int ntc = (L.nt + kWave - 1) / kWave;
-    const int nac = (L.na + kWave - 1) / kWave;
-    const int nbc = (L.nb + kWave - 1) / kWave;
+    const bool two = AP == 1 && 2 * n <= kWave;
     float m[AP], sc[AP][C];
     bool own[AP];
 #pragma unroll
     for (int a = 0; a < AP; ++a) {
-      const int at = lane + kWave * a;
+      const int at = (two ? lane & (kWave / 2 - 1) : lane) + kWave * a;
       own[a] = at < n;
       m[a] = own[a] ? ((gfloat*)L.mass)[at] : 0.f;
 #pragma unroll
       for (int c = 0; c < C; ++c)
         sc[a][c] = own[a] ? ((gfloat*)L.scale)[at * C + c] : 0.f;
     }
-    const int64_t nseg = e - s;
-    for (int64_t gi = wv; gi * kUknWaveGroup < nseg; gi += kUknWaves) {
-      const int64_t q0 = s + gi * kUknWaveGroup;
-      const int64_t q1 = q0 + kUknWaveGroup < e ? q0 + kUknWaveGroup : e;
-      for (int64_t q = q0; q < q1; ++q) {
-        const gfloat* xq = (const gfloat*)J.xs + (size_t)(q - J.first) * n * 3;
-        float x[AP][3];
-#pragma unroll
-        for (int a = 0; a < AP; ++a)
-#pragma unroll
-          for (int d = 0; d < 3; ++d)
-            x[a][d] = own[a] ? xq[(lane + kWave * a) * 3 + d] : 0.f;
-#pragma unroll
-        for (int a = 0; a < AP; ++a)
-          if (own[a])
-            pos[lane + kWave * a] =
-                make_float4(x[a][0], x[a][1], x[a][2], m[a]);
-        // the first atom's cell records load during the torsions, the
-        // second's (AP = 2) during the angles and bonds: one record set in
-        // registers at a time
-        float psi[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) psi[c] = 0.f;
-        Corners<C> cn;
-        if (own[0]) grid_fetch<C>(g, x[0][0], x[0][1], x[0][2], cn);
-        wave_fence();
-        // bonded terms, energies only, every chunk of the ligand
-        float eb = 0.f, ea = 0.f, et = 0.f;
-        for (int ch = 0; ch < ntc; ++ch) {
-          const int t = ch * kWave + lane;
-          if (t < L.nt)
-            et += torsion_term<false>(pos, sh.tijkl[t], sh.tpar[t],
-                                      no_forces);
+    // the wavefront's share: pairs of samples, in order
+    const int64_t pairs = (e - s + 1) / 2;
+    const int64_t s0 = s + 2 * (pairs * wv / kUknWaves);
+    const int64_t s1 = wv + 1 < kUknWaves
+                           ? s + 2 * (pairs * (wv + 1) / kUknWaves) : e;
+    for (int64_t q0 = s0; q0 < s1; q0 += kUknWaveGroup) {
+      const int64_t q1 = q0 + kUknWaveGroup < s1 ? q0 + kUknWaveGroup : s1;
+      if constexpr (AP == 1) {
+        if (two) {
+          ukn_group<C, 1, 2>(g, L, J, sh, ew, pos, col, m, sc, own, q0, q1,
+                             lane);
+          continue;
         }
-#pragma unroll
-        for (int a = 0; a < AP; ++a) {
-          if (own[a]) {
-            float ev[C], dv[C][3];
-            grid_finish<C, false>(g, cn, sc[a], ev, dv);
-#pragma unroll
-            for (int c = 0; c < C; ++c) psi[c] += ev[c];
-          }
-          if (a + 1 < AP && own[a + 1])
-            grid_fetch<C>(g, x[a + 1][0], x[a + 1][1], x[a + 1][2], cn);
-          if (a + 1 < AP) {
-            for (int ch = 0; ch < nac; ++ch) {
-              const int t = ch * kWave + lane;
-              if (t < L.na)
-                ea += angle_term<false>(pos, sh.aijk[t], sh.apar[t],
-                                        no_forces);
-            }
-            for (int ch = 0; ch < nbc; ++ch) {
-              const int t = ch * kWave + lane;
-              if (t < L.nb)
-                eb += bond_term<false>(pos, sh.bij[t], sh.bpar[t], no_forces);
-            }
-          }
-        }
-        for (int ch = 0; AP == 1 && ch < nac; ++ch) {
-          const int t = ch * kWave + lane;
-          if (t < L.na)
-            ea += angle_term<false>(pos, sh.aijk[t], sh.apar[t], no_forces);
-        }
-        for (int ch = 0; AP == 1 && ch < nbc; ++ch) {
-          const int t = ch * kWave + lane;
-          if (t < L.nb)
-            eb += bond_term<false>(pos, sh.bij[t], sh.bpar[t], no_forces);
-        }
-        // the centre of mass
-        float px = 0.f, py = 0.f, pz = 0.f;
-#pragma unroll
-        for (int a = 0; a < AP; ++a) {
-          px += m[a] * x[a][0];
-          py += m[a] * x[a][1];
-          pz += m[a] * x[a][2];
-        }
-        wave_sumf3(px, py, pz);
-        const double U0b = wave_sum((double)eb + (double)ea + (double)et);
-        double ps[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) ps[c] = wave_sum((double)psi[c]);
-        const float cx = px * L.inv_total_mass - L.site[0];
-        const float cy = py * L.inv_total_mass - L.site[1];
-        const float cz = pz * L.inv_total_mass - L.site[2];
-        const float d = sqrtf(cx * cx + cy * cy + cz * cz);
-        const float excess = d - L.d0;
-        const double ui =
-            excess > 0.f
-                ? 0.5 * (double)L.krest * (double)excess * (double)excess
-                : 0.0;
-        const double U0 = U0b + 0.0 + 0.0 + ui;
-        double* cs = col + (q - q0) * K;
-        for (int k = lane; k < K; k += kWave) {
-          double E = U0;
-#pragma unroll
-          for (int c = 0; c < C; ++c) E = fma(ew[k * C + c], ps[c], E);
-          cs[k] = ew[K * C + k] * E;
-        }
-        // the next sample's position stores come after every lane's
-        // reads of this one
-        wave_fence();
       }
-      // the group's columns, row by row: a run of consecutive samples of
-      // each row by consecutive lanes
-      wave_fence();
-      const int cnt = (int)(q1 - q0);
-      const int64_t n0 = q0 - J.first;
-      auto out = BPMF_GMEM(double, J.ukn);
-      for (int i = lane; i < cnt * K; i += kWave) {
-        const int k = i / cnt, qq = i - k * cnt;
-        out[(size_t)k * J.ld + n0 + qq] = col[qq * K + k];
-      }
-      wave_fence();
+      ukn_group<C, AP, 1>(g, L, J, sh, ew, pos, col, m, sc, own, q0, q1, lane);
     }
     s = e;
   }

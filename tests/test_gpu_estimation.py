@@ -48,6 +48,33 @@ def test_energy_matrix_matches_brute_force_ukn():
     ctx.close()
 
 
+@pytest.mark.parametrize("atoms,N", [(31, 1), (32, 2), (32, 3), (32, 67),
+                                     (33, 9), (64, 65), (65, 9)])
+def test_energy_matrix_wavefront_edges(atoms, N):
+    """Ligands around two samples to a wavefront (32 atoms) and one (64), and
+    sample counts that leave a half, a wavefront or a group short: against
+    brute force (the tolerance above), each column the bits of the sample
+    alone."""
+    print_case(f"energy_matrix edges {atoms} atoms {N} samples")
+    g = synth.make_system(1).grid
+    rng = np.random.default_rng([5, atoms, N])
+    lig = synth.make_ligand(rng, atoms, 6)
+    xs = _samples(lig, rng, N)
+    ctx, (lid,) = make_context(g, [lig], seed=1)
+    x = dev(xs, torch.float32)
+    u = ctx.energy_matrix(lid, x)
+    for i in {0, N // 2, N - 1}:
+        assert torch.equal(ctx.energy_matrix(lid, x[i:i + 1].clone())[:, 0],
+                           u[:, i])
+    og, ol = oracle.OGrid(g), oracle.OLigand(lig)
+    u64 = oracle.ukn(og, ol, xs)
+    _, mags = oracle.components(og, ol, xs)
+    beta = 1.0 / (oracle.R_GAS * lig.T)
+    assert np.all(np.abs(u.cpu().numpy() - u64) <=
+                  1e-5 * beta[:, None] * mags.sum(axis=1)[None, :] + 1e-12)
+    ctx.close()
+
+
 def test_energy_matrix_full_size_config2_sampled_entries():
     """64 states x 32000 samples (the production u_kn of the 48-atom
     system), checked on 1000 sampled entries against brute force."""
