@@ -135,8 +135,6 @@ struct bpmf_ctx {
   size_t mlp_bytes = 0;
   void* train_mem = nullptr;  // proposal training: activations, partial sums
   size_t train_bytes = 0;
-  void* place_mem = nullptr;  // centres of mass of placed configurations
-  size_t place_bytes = 0;
   // this device's address of the no-allocation job table (or null)
   void* scratch_addr = nullptr;
   // batched pose moves over every ligand with a proposal: per-ligand
@@ -426,7 +424,6 @@ extern "C" int bpmf_destroy(bpmf_ctx* c) {
   }
   c->dfree(c->mlp_mem);
   c->dfree(c->train_mem);
-  c->dfree(c->place_mem);
   c->dfree(c->grid_mem);
   c->dfree(c->d_ligs);
   c->dfree(c->d_tasks);
@@ -1959,13 +1956,9 @@ extern "C" int bpmf_place_poses(bpmf_ctx* c, int ligand_id,
                 (long long)total);
   if (count == 0) return BPMF_OK;
   if (!dev_confs || !dev_out) return fail(BPMF_E_INVAL, "null pose buffer");
-  if ((rc = ensure_scratch(c, &c->place_mem, &c->place_bytes,
-                           (size_t)n_conf * 3 * sizeof(double))))
-    return rc;
   HIP_TRY(launch_place_poses(c->d_ligs + ligand_id, c->ligs[ligand_id].dev.n,
-                             dev_confs, n_conf, n_com, n_orient, first, count,
-                             (double*)c->place_mem, c->seed, dev_out,
-                             c->stream));
+                             dev_confs, n_com, n_orient, first, count,
+                             c->seed, dev_out, c->stream));
   return BPMF_OK;
 }
 

@@ -162,6 +162,35 @@ def test_placements_match_oracle():
     ctx.close()
 
 
+@pytest.mark.parametrize("confs,coms,orients,first,count",
+                         [(1, 1, 1, 0, 1), (63, 1, 1, 0, 63), (65, 1, 1, 0, 65),
+                          (2, 5, 13, 1, 64), (2, 5, 13, 66, 64)])
+def test_placements_block_edges(confs, coms, orients, first, count):
+    """Ranges around a block's 64 poses, a configuration to a pose and many,
+    written to a 16-byte address and past one: the oracle (tolerance above),
+    and nothing outside the range."""
+    print_case(f"placement edges {confs} {coms} {orients} {first} {count}")
+    system = synth.make_system(1)
+    lig, g = system.ligands[0], system.grid
+    ctx, (lid,) = make_context(g, [lig], seed=78)
+    rng = np.random.default_rng(confs)
+    x = np.asarray(lig.x0[0] + rng.normal(scale=0.3, size=(
+        confs, lig.n_atoms, 3)), np.float32)
+    ref = P.placements(x.astype(np.float64),
+                       lig.mass.astype(np.float32).astype(np.float64),
+                       np.asarray(lig.site_center, np.float32),
+                       np.float32(lig.d0), coms, orients, seed=78, lig=lid)
+    got = ctx.place_poses(lid, dev(x, torch.float32), coms, orients,
+                          first=first, count=count)
+    assert np.abs(got.cpu().numpy() - ref[first:first + count]).max() < 2e-5
+    room = torch.full((got.numel() + 2,), 7.0, device=got.device)
+    ctx.place_poses(lid, dev(x, torch.float32), coms, orients, first=first,
+                    count=count, out=room[1:-1].view(got.shape))
+    assert torch.equal(room[1:-1].view(got.shape), got)
+    assert room[0] == 7.0 and room[-1] == 7.0
+    ctx.close()
+
+
 def _init_system(n_seeds, capacity):
     system = synth.make_system(1)
     g, (lig,) = synth.add_soft_grids(system.grid, system.ligands[:1])
