@@ -65,6 +65,49 @@ __device__ __forceinline__ void hct(float r, float ir, float a, float s,
   }
 }
 
+// The same without branches, from r^2 and 1/r: every lane of a wavefront has
+// pairs on either side of each condition, so the branches were walked both
+// ways, and no two partners' chains overlapped.  ra = rcp(a).  The fused and
+// the separate roundings are hct's (contracted) ones, so the values are its.
+// __logf for a normal argument (u x is at least a / (r + s)): its scaling of
+// subnormal arguments and its care of infinities left out, the same value
+__device__ __forceinline__ float hct_log(float v) {
+  constexpr float kLn2 = 0x1.62e42ep-1f, kLn2Low = 0x1.efa39ep-25f;
+  const float y = __builtin_amdgcn_logf(v);  // log2
+  return fmaf(y, kLn2, fmaf(y, kLn2Low, fmaf(y, kLn2, -(y * kLn2))));
+}
+template <bool DERIV>
+__device__ __forceinline__ void hct_flat(float r2, float ir, float a, float ra,
+                                         float s, float& H, float& dH) {
+#pragma clang fp contract(off)
+  const float r = r2 * ir, rps = fmaf(r2, ir, s), rs = r - s;
+  const float ars = fabsf(rs);
+  const bool shell = a > ars;  // the shells start at a, not at |r - s|
+  const float u = __builtin_amdgcn_rcpf(rps);
+  const float l = shell ? ra : __builtin_amdgcn_rcpf(ars);
+  const float lg = hct_log(u * (shell ? a : ars));
+  const float s2r2 = fmaf(s, s, -(r * r));
+  const float uu = u * u;
+  const float l2u2 = fmaf(l, l, -uu);
+  const bool none = a >= rps, inside = a < s - r;
+  float h = ir * (0.125f * s2r2 * l2u2);
+  h = fmaf(0.5f, l - u, h);
+  h = fmaf(ir, 0.25f * lg, h);
+  h = inside ? h + (ra - l) : h;
+  H = none ? 0.f : h;
+  if (DERIV) {
+    const float dll = shell ? 0.f : (rs > 0.f ? -l : l);
+    const float dl = l * dll;
+    float d = fmaf(ir, ir * (-0.125f * s2r2), -0.25f) * l2u2;
+    d = fmaf(0.5f, fmaf(u, u, dl), d);
+    d = fmaf(ir, 0.25f * s2r2 * fmaf(dl, l, u * uu), d);
+    d = fmaf(ir, 0.25f * (-u - dll), d);
+    d = fmaf(ir, ir * (-0.25f * lg), d);
+    d = inside ? d - dl : d;
+    dH = none ? 0.f : d;
+  }
+}
+
 struct PairDev {
   int n;
   const float4* p0;       // n: q, sigma, sqrt(eps), rho

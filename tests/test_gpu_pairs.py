@@ -94,6 +94,29 @@ def test_pair_terms_90_atoms_two_wavefronts():
     ctx.close()
 
 
+@pytest.mark.parametrize("n,N", [(3, 86), (31, 9), (32, 8), (33, 8), (64, 3),
+                                 (64, 4), (65, 4), (128, 3)])
+def test_pair_terms_packing_edges(n, N):
+    """Sizes around a mask word, a wavefront and the largest whose derivatives
+    are kept, with the last workgroup full or short: the first and the last
+    configuration against the oracle, and each the bits of itself alone."""
+    print_case(f"pairs packing {n} atoms {N} configurations")
+    rng = np.random.default_rng([6, n])
+    lig = synth.make_ligand(rng, n, 2, box=8.0)
+    system = synth.make_system(1)
+    ctx, (lid,) = make_context(system.grid, [lig], seed=1)
+    p = synth.pair_params(lig, seed=3)
+    ctx.pair_setup(lid, p)
+    xs = (lig.x0[0] + rng.normal(scale=0.1, size=(N, n, 3))).astype(np.float32)
+    _check(ctx, lid, xs[[0, N - 1]], p, fd_atoms=[0, n - 1])
+    x = dev(xs, torch.float32)
+    terms, F = ctx.pair_evaluate(lid, x)
+    for c in {0, N // 2, N - 1}:
+        t1, F1 = ctx.pair_evaluate(lid, x[c:c + 1].clone())
+        assert torch.equal(t1[0], terms[c]) and torch.equal(F1[0], F[c])
+    ctx.close()
+
+
 def test_pair_terms_close_spheres_reach_every_branch():
     print_case("pairs close spheres")
     x = np.array([[0.0, 0.0, 0.0], [0.35, 0.0, 0.0], [0.0, 2.6, 0.3]])
