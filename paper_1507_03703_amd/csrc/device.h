@@ -678,6 +678,22 @@ __device__ __forceinline__ void block_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// Partners whose chains of a pass run side by side (pair_stage).  A replica's
+// wavefronts share one CU and issue for some three quarters of the time, so
+// what overlaps chains must not add instructions: 48 atoms on 8 wavefronts
+// have 6 partners a thread, and 20 sweeps of 20 steps take 3.21 ms with 3 at
+// a time, 3.36 with 2 or with 4 (two idle of 8), 3.40 with 6, 4.31 with 8;
+// one at a time through branches 3.63 ms.
+constexpr int kPairAhead = 3;
+
+// a pair's force factor; its two terms are rounded before their sum
+__device__ __forceinline__ float pair_force(float flj, float fcl, float c14,
+                                            bool off) {
+#pragma clang fp contract(off)
+  const float f = flj + fcl * c14;
+  return off ? 0.f : f;
+}
+
 // The ligand's intramolecular nonbonded and OBC GB/SA energy (the terms of
 // bpmf_pair_evaluate) for the configuration in sh.pos.  Every atom's row of
 // pair terms (each pair is visited from both ends, so forces need no
@@ -706,6 +722,18 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
   const bool own = tid < n;  // slice 0's thread of atom tid
   const int j0 = k * n / S, j1 = (k + 1) * n / S;
   float* const part = sh.pscr + (size_t)(k * n + i) * 9;
+  // the owner's sums over the slices, in order: 8 (the widest block), or any
+  // number, the loads ahead of the additions
+  auto slices = [&](auto add) {
+    const float* o = sh.pscr + (size_t)tid * 9;
+    if (S == 8) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) add(o + q * n * 9);
+    } else {
+#pragma unroll 2
+      for (int q = 0; q < S; ++q) add(o + q * n * 9);
+    }
+  };
   float4 xi = make_float4(0.f, 0.f, 0.f, 0.f), pi = xi;
   float2 qi1 = make_float2(0.f, 0.f);
   if (act) {
@@ -717,41 +745,40 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
   if (act) {
     float I = 0.f, e_lj = 0.f, e_c = 0.f, fx = 0.f, fy = 0.f, fz = 0.f;
     float vx = 0.f, vy = 0.f, vz = 0.f;
-    for (int j = j0; j < j1; ++j) {
-      if (j == i) continue;
+    const float ra = __builtin_amdgcn_rcpf(qi1.x);
+    for (int jb = j0; jb < j1; jb += kPairAhead)
+#pragma unroll
+    for (int u = 0; u < kPairAhead; ++u) {
+      const int j = jb + u < j1 ? jb + u : j1 - 1;
+      const bool self = jb + u >= j1 || j == i;  // or past the slice
       const float4 xj = sh.pos[j], pj = sh.pp0[j];
       const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
       const float r2 = dx * dx + dy * dy + dz * dz;
-      const float ir = __builtin_amdgcn_rsqf(r2), r = r2 * ir;
-      float H, dH;
-      hct(r, ir, qi1.x, sh.pp1[j].y, H, dH);
-      I += H;
+      const float ir = __builtin_amdgcn_rsqf(r2);
+      float H, dH = 0.f;
+      hct<FORCES, false>(r2, ir, qi1.x, ra, sh.pp1[j].y, H, dH);
+      I += self ? 0.f : H;
       if (FORCES) {
-        const float h = dH * ir;
+        const float h = self ? 0.f : dH * ir;
         vx += h * dx;
         vy += h * dy;
         vz += h * dz;
       }
       const int w = i * kPairWords + (j >> 5);
       const uint32_t bit = 1u << (j & 31);
-      if (sh.pex[w] & bit) continue;
+      const bool off = self || (sh.pex[w] & bit), f14 = sh.p14[w] & bit;
       const float sg = 0.5f * (pi.y + pj.y), ep = pi.z * pj.z;
       const float ir2 = ir * ir;
       const float sr2 = sg * sg * ir2, sr6 = sr2 * sr2 * sr2;
-      float lj = 4.f * ep * (sr6 * sr6 - sr6);
-      float flj = 24.f * ep * (2.f * sr6 * sr6 - sr6) * ir2;
-      float cl = P.kc * pi.x * pj.x * ir;
-      float fcl = cl * ir2;
-      if (sh.p14[w] & bit) {
-        lj *= P.lj14;
-        flj *= P.lj14;
-        cl *= P.el14;
-        fcl *= P.el14;
-      }
-      e_lj += 0.5f * lj;
-      e_c += 0.5f * cl;
+      const float l14 = f14 ? P.lj14 : 1.f, c14 = f14 ? P.el14 : 1.f;
+      const float lj = 4.f * ep * (sr6 * sr6 - sr6) * l14;
+      const float cl = P.kc * pi.x * pj.x * ir;
+      e_lj += 0.5f * (off ? 0.f : lj);
+      e_c += 0.5f * (off ? 0.f : cl * c14);
       if (FORCES) {
-        const float f = flj + fcl;
+        const float flj =
+            24.f * ep * (2.f * sr6 * sr6 - sr6) * ir2 * l14;
+        const float f = pair_force(flj, cl * ir2, c14, off);
         fx += f * dx;
         fy += f * dy;
         fz += f * dz;
@@ -773,8 +800,7 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
   float Ri = 0.f, dRdI = 0.f;
   if (own) {
     float I = 0.f;
-    for (int q = 0; q < S; ++q) {
-      const float* o = sh.pscr + (size_t)(q * n + tid) * 9;
+    slices([&](const float* o) {
       I += o[0];
       e_lj += o[1];
       e_c += o[2];
@@ -784,7 +810,7 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
       vx += o[6];
       vy += o[7];
       vz += o[8];
-    }
+    });
     const float psi = I * qi1.x;
     const float t = psi * (kObcA - psi * (kObcB - kObcC * psi));
     const float th = tanhf(t);
@@ -798,26 +824,31 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
   if (act) {
     const float qi = pi.x, Rii = sh.pR[i];
     float e_gb = 0.f, dEdR = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-    for (int j = j0; j < j1; ++j) {
-      if (j == i) continue;
+    const float kqi = P.kgb * qi;
+    for (int jb = j0; jb < j1; jb += kPairAhead)
+#pragma unroll
+    for (int u = 0; u < kPairAhead; ++u) {
+      const int j = jb + u < j1 ? jb + u : j1 - 1;
       const float4 xj = sh.pos[j];
       const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
       const float r2 = dx * dx + dy * dy + dz * dz;
       const float Rj = sh.pR[j];
       const float RR = Rii * Rj;
       const float iRR = __builtin_amdgcn_rcpf(RR);
-      const float D = __expf(-0.25f * r2 * iRR);
+      const float t = 0.25f * r2 * iRR;
+      const float D = __expf(-t);
       const float f2 = r2 + RR * D;
-      const float invf = rsqrtf(f2);
+      const float invf = __builtin_amdgcn_rsqf(f2);  // f2 is normal
       const float invf3 = invf * invf * invf;
-      const float kq = P.kgb * qi * sh.pp0[j].x;
+      const float kq =
+          (jb + u >= j1 || j == i ? 0.f : kqi) * sh.pp0[j].x;
       e_gb += 0.5f * kq * invf;
       if (FORCES) {
         const float g = kq * (1.f - 0.25f * D) * invf3;
         gx += g * dx;
         gy += g * dy;
         gz += g * dz;
-        dEdR -= 0.5f * kq * Rj * D * (1.f + 0.25f * r2 * iRR) * invf3;
+        dEdR -= 0.5f * kq * Rj * D * (1.f + t) * invf3;
       }
     }
     part[0] = e_gb;
@@ -831,14 +862,13 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
   if (own) {
     const float qi = pi.x;
     float dEdR = 0.f;
-    for (int q = 0; q < S; ++q) {
-      const float* o = sh.pscr + (size_t)(q * n + tid) * 9;
+    slices([&](const float* o) {
       e_gb += o[0];
       dEdR += o[1];
       fx += o[2];
       fy += o[3];
       fz += o[4];
-    }
+    });
     // the atom's self term
     e_gb += 0.5f * P.kgb * qi * qi / Ri;
     dEdR -= 0.5f * P.kgb * qi * qi / (Ri * Ri);
@@ -854,16 +884,20 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
     // the atom's own from v_i
     if (act) {
       float gx = 0.f, gy = 0.f, gz = 0.f;
-      for (int j = j0; j < j1; ++j) {
-        if (j == i) continue;
+      for (int jb = j0; jb < j1; jb += kPairAhead)
+#pragma unroll
+      for (int u = 0; u < kPairAhead; ++u) {
+        const int j = jb + u < j1 ? jb + u : j1 - 1;
         const float4 xj = sh.pos[j];
         const float2 pj1 = sh.pp1[j];
         const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
         const float r2 = dx * dx + dy * dy + dz * dz;
-        const float ir = __builtin_amdgcn_rsqf(r2), r = r2 * ir;
+        const float ir = __builtin_amdgcn_rsqf(r2);
         float Hj, dHj;
-        hct(r, ir, pj1.x, qi1.y, Hj, dHj);
-        const float g = -sh.pb[j] * dHj * ir;
+        hct<true, true>(r2, ir, pj1.x, __builtin_amdgcn_rcpf(pj1.x), qi1.y, Hj,
+                        dHj);
+        const float gj = -sh.pb[j] * dHj * ir;
+        const float g = jb + u >= j1 || j == i ? 0.f : gj;
         gx += g * dx;
         gy += g * dy;
         gz += g * dz;
@@ -878,12 +912,11 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
       fx -= bi * vx;
       fy -= bi * vy;
       fz -= bi * vz;
-      for (int q = 0; q < S; ++q) {
-        const float* o = sh.pscr + (size_t)(q * n + tid) * 9;
+      slices([&](const float* o) {
         fx += o[0];
         fy += o[1];
         fz += o[2];
-      }
+      });
     }
   }
   e = own ? e_lj + e_c + e_gb + e_sa : 0.f;

@@ -27,58 +27,26 @@ __host__ __device__ inline int pair_lds_bytes(int n, int waves) {
 
 constexpr float kObcA = 1.0f, kObcB = 0.8f, kObcC = 4.85f;
 
-// descreening integral H(r; a, s) of a ball of radius s at distance r
-// outside radius a (Hawkins, Cramer, Truhlar), and dH/dr; ir = 1/r.  The
-// reciprocals and the logarithm are the hardware's (1 ulp); du/u = -u and
-// dl/l = -+l are used as such.
-__device__ __forceinline__ void hct(float r, float ir, float a, float s,
-                                   float& H, float& dH) {
-  if (a >= r + s) {
-    H = 0.f;
-    dH = 0.f;
-    return;
-  }
-  const float u = __builtin_amdgcn_rcpf(r + s), du = -u * u;
-  const float rs = r - s;
-  float l, dl, dll, x;  // dll = dl / l; x = 1 / l
-  if (a > fabsf(rs)) {
-    x = a;
-    l = __builtin_amdgcn_rcpf(a);
-    dl = 0.f;
-    dll = 0.f;
-  } else {
-    x = fabsf(rs);
-    l = __builtin_amdgcn_rcpf(x);
-    dl = rs > 0.f ? -l * l : l * l;
-    dll = rs > 0.f ? -l : l;
-  }
-  const float s2r2 = s * s - r * r;
-  const float l2u2 = l * l - u * u;
-  const float lg = __logf(u * x);
-  H = 0.5f * (l - u) + 0.125f * s2r2 * l2u2 * ir + 0.25f * lg * ir;
-  dH = 0.5f * (dl - du) + (-0.25f - 0.125f * s2r2 * ir * ir) * l2u2 +
-       0.25f * s2r2 * (l * dl - u * du) * ir +
-       0.25f * (-u - dll) * ir - 0.25f * lg * ir * ir;
-  if (a < s - r) {  // atom i inside the ball: the shells a .. s - r whole
-    H += __builtin_amdgcn_rcpf(a) - l;
-    dH -= dl;
-  }
-}
-
-// The same without branches, from r^2 and 1/r: every lane of a wavefront has
-// pairs on either side of each condition, so the branches were walked both
-// ways, and no two partners' chains overlapped.  ra = rcp(a).  The fused and
-// the separate roundings are hct's (contracted) ones, so the values are its.
-// __logf for a normal argument (u x is at least a / (r + s)): its scaling of
-// subnormal arguments and its care of infinities left out, the same value
+// Descreening integral H(r; a, s) of a ball of radius s at distance r outside
+// radius a (Hawkins, Cramer, Truhlar), and dH/dr, from r^2 and ir = 1/r; ra =
+// rcp(a).  The reciprocals and the logarithm are the hardware's (1 ulp);
+// du/u = -u and dl/l = -+l are used as such.  Without branches: every lane of
+// a wavefront has pairs on either side of each condition, so branches would
+// be walked both ways, and partners' chains would not overlap.  Roundings are
+// placed by hand, so that every caller gets the same bits; OWN: s is the
+// atom's own for all partners (s^2 rounded by itself).
+//
+// The logarithm is __logf for a normal argument (u x is at least a / (r + s)):
+// its scaling of subnormal arguments and its care of infinities left out, the
+// same value.
 __device__ __forceinline__ float hct_log(float v) {
   constexpr float kLn2 = 0x1.62e42ep-1f, kLn2Low = 0x1.efa39ep-25f;
   const float y = __builtin_amdgcn_logf(v);  // log2
   return fmaf(y, kLn2, fmaf(y, kLn2Low, fmaf(y, kLn2, -(y * kLn2))));
 }
-template <bool DERIV>
-__device__ __forceinline__ void hct_flat(float r2, float ir, float a, float ra,
-                                         float s, float& H, float& dH) {
+template <bool DERIV, bool OWN>
+__device__ __forceinline__ void hct(float r2, float ir, float a, float ra,
+                                    float s, float& H, float& dH) {
 #pragma clang fp contract(off)
   const float r = r2 * ir, rps = fmaf(r2, ir, s), rs = r - s;
   const float ars = fabsf(rs);
@@ -86,7 +54,7 @@ __device__ __forceinline__ void hct_flat(float r2, float ir, float a, float ra,
   const float u = __builtin_amdgcn_rcpf(rps);
   const float l = shell ? ra : __builtin_amdgcn_rcpf(ars);
   const float lg = hct_log(u * (shell ? a : ars));
-  const float s2r2 = fmaf(s, s, -(r * r));
+  const float s2r2 = OWN ? fmaf(-r, r, s * s) : fmaf(s, s, -(r * r));
   const float uu = u * u;
   const float l2u2 = fmaf(l, l, -uu);
   const bool none = a >= rps, inside = a < s - r;

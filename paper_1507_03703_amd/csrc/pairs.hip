@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kPairThreads) void k_pair_terms(
         const float r2 = dx * dx + dy * dy + dz * dz;
         const float ir = __builtin_amdgcn_rsqf(r2);
         float H, dH = 0.f;
-        hct_flat<FORCES>(r2, ir, qi1.x, ra, s_p1[j].y, H, dH);
+        hct<FORCES, false>(r2, ir, qi1.x, ra, s_p1[j].y, H, dH);
         I += self ? 0.f : H;
         if (FORCES) {
           const float h = self ? 0.f : dH * ir;
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kPairThreads) void k_pair_terms(
         const float ir = __builtin_amdgcn_rsqf(r2);
         const float aj = s_p1[j].x;
         float H, dH;
-        hct_flat<true>(r2, ir, aj, __builtin_amdgcn_rcpf(aj), qi1.y, H, dH);
+        hct<true, true>(r2, ir, aj, __builtin_amdgcn_rcpf(aj), qi1.y, H, dH);
         h = j == i ? 0.f : dH * ir;
       }
       h *= s_b[j];

@@ -261,6 +261,22 @@ def test_pair_terms_in_the_sampled_energy(n, waves):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,waves", [(3, 8), (25, 8), (26, 4), (65, 8)])
+def test_pair_slices_of_uneven_length(n, waves):
+    """Slices of a thread's partners that are shorter than, longer than and no
+    multiple of the three taken side by side (down to an empty one): lock-step
+    sweeps against the oracle."""
+    print_case("pair slices", n, waves)
+    g, lig, p = _full_pathway_system(n, K=3)
+    og = oracle.OGrid(g)
+    ctx, (lid,) = make_context(g, [lig], seed=18)
+    ctx.set_waves(waves)
+    ctx.pair_setup(lid, p)
+    ctx.pair_sample(lid, True)
+    lockstep(ctx, og, [(lid, lig)], 18, 2, 5, "pairs", pairs={lid: p})
+    ctx.close()
+
+
 def test_pair_sample_needs_parameters():
     print_case("pair_sample errors")
     g, lig, p = _full_pathway_system(12, K=2)
