@@ -1092,7 +1092,8 @@ __device__ __forceinline__ void ukn_group(const GridDev& g, const LigDev& L,
     const float cx = px * L.inv_total_mass - L.site[0];
     const float cy = py * L.inv_total_mass - L.site[1];
     const float cz = pz * L.inv_total_mass - L.site[2];
-    const float d = sqrtf(cx * cx + cy * cy + cz * cz);
+    // fused as the block evaluation fuses it, whatever is inlined here
+    const float d = sqrtf(fmaf(cz, cz, fmaf(cx, cx, cy * cy)));
     const float excess = d - L.d0;
     const double ui = excess > 0.f
                           ? 0.5 * (double)L.krest * (double)excess *
