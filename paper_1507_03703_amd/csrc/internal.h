@@ -195,8 +195,8 @@ hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
                             hipStream_t st);
 hipError_t launch_sweep_tail(const LigDev* d_ligs, int n_ligs,
                              int exchange_every, int scheme, int max_sep,
-                             int n_sub, int sample_every, uint64_t seed,
-                             hipStream_t st);
+                             int n_sub, int sample_every, bool far,
+                             uint64_t seed, hipStream_t st);
 hipError_t launch_sweep_begin(const LigDev* d_ligs, int n_ligs,
                               hipStream_t st);
 hipError_t launch_sweep_finish(const LigDev* d_ligs, int n_ligs,
@@ -204,8 +204,25 @@ hipError_t launch_sweep_finish(const LigDev* d_ligs, int n_ligs,
                                uint64_t seed, hipStream_t st);
 // n_sub exchange sweeps in a row (sweep j draws with replica field j)
 hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
-                           int max_sep, int n_sub, uint64_t seed,
+                           int max_sep, int n_sub, bool far, uint64_t seed,
                            hipStream_t st);
+// All-separations exchange of K states: up to this separation the residue
+// classes are walked by a wavefront each, eight at a time; past it, where there
+// are many classes of few states, by a lane each, and the exchange of a ladder
+// that goes past it (`far` above) has kernels of its own.  The line is where
+// both cost the same: a wavefront's walk of a class costs 0.7 us however short
+// the class, all lanes' walks together 0.3 to 1 us by its length.  One sweep
+// over every separation, a wavefront for each class and this way: 64 states
+// 244 and 91 us, 170 states 1433 and 264 us, 256 states 3096 and 432 us (549 us
+// with one lane per first state following its run); up to 12 separations of
+// 16 states, five sweeps: 110 and 92 us; of 256 states: 173 us by wavefronts,
+// 248 us by lanes.
+__host__ __device__ constexpr int exchange_wave_separations(int K) {
+  return K <= 64 ? 8 : K <= 192 ? 16 : 24;
+}
+inline bool exchange_far(int K, int max_sep) {
+  return (max_sep < K - 1 ? max_sep : K - 1) > exchange_wave_separations(K);
+}
 // one ligand's share of an energy-matrix launch: samples xs (n x n_atoms x
 // 3), output u_kn (K x ld); its samples are [first, first + n) of the
 // launch's flat sample index

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "deferred.h"
 #include "device.h"
 #include "internal.h"
@@ -116,9 +118,11 @@ __device__ bool attempt_pair(const LigDev& L, int a, int b, int sep,
 // length in steps, as when one lane per first position follows its run step
 // by step (170 states, 25 sweeps of 5 separations, neighbours swapping at
 // 0.87: 926 us a call so, 334 us this way).  kXAhead: 4, 6 and 8 steps give
-// 372, 355 and 354 us; with the walk's doublings as well, 334.  The energies are the same
-// double sums as state_energy and each attempt sees the replicas the
-// one-thread order gives it, so every decision is that order's.
+// 372, 355 and 354 us; with the walk's doublings as well, 334.  Separations of
+// many short classes are walked by a lane per class instead
+// (exchange_wave_separations).  The energies are the same double sums as
+// state_energy and each attempt sees the replicas the one-thread order gives
+// it, so every decision is that order's.
 constexpr int kXStates = 256, kXChannels = 5;
 constexpr int kXAhead = 8;      // steps decided ahead of the walk
 constexpr int kXHalf = kXAhead / 2;
@@ -274,7 +278,63 @@ __device__ __forceinline__ void exchange_class(XStage& X, const double* em,
   }
 }
 
+// Step 3 for a class by one lane, for separations of many short classes: the
+// positions in order, each either passing its replica on to the next one or
+// keeping the run's.  The states' replicas and run lengths load kXLane
+// positions at a time, ahead of the chain; a run still open after its kXAhead
+// steps goes on attempt by attempt.
+constexpr int kXLane = 4;
 template <int C, bool TABLE>
+__device__ __forceinline__ void exchange_lane(XStage& X, const double* em,
+                                              int K, int d, int rho, int cur,
+                                              int lb) {
+  const int* ros = X.ros[cur];
+  const double2* el = X.el[lb];
+  int rq = 0, left = 0;  // the run's replica, its known swaps still to come
+  bool start = true, open = false;
+  for (int a0 = rho; a0 < K; a0 += kXLane * d) {
+    int rep[kXLane + 1], ln[kXLane];
+#pragma unroll
+    for (int m = 0; m <= kXLane; ++m) {
+      const int a = a0 + m * d < K ? a0 + m * d : a0;
+      rep[m] = ros[a];
+      if (m < kXLane) {
+        const int l0 = X.len[0][a], l1 = X.len[1][a];
+        ln[m] = l0 == kXHalf ? l0 + l1 : l0;
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < kXLane; ++m) {
+      const int a = a0 + m * d, b = a + d;
+      if (a >= K) break;
+      if (start) {
+        rq = rep[m];
+        left = ln[m];
+        open = left == kXAhead;
+      }
+      bool swap = left > 0;
+      if (!swap && open && b < K) {
+        double ua[1 + C], ub[1 + C], cv[1 + C];
+        staged_load<C>(X.sw + a * (1 + C), ua);
+        staged_load<C>(X.sw + b * (1 + C), ub);
+        if (!TABLE) staged_load<C>(X.cp + rq * (1 + C), cv);
+        const double e0 = TABLE ? em[a * kXTable + rq] : staged_sum<C>(cv, ua);
+        const double e1 = TABLE ? em[b * kXTable + rq] : staged_sum<C>(cv, ub);
+        swap = staged_accepts(ua[C], ub[C], el[a], e0, e1, X.ecur[b]);
+        open = swap;
+      } else {
+        --left;
+      }
+      X.ros[cur ^ 1][a] = swap ? rep[m + 1] : rq;
+      start = !swap;
+    }
+  }
+}
+
+// FAR: some separation is past exchange_wave_separations (a kernel of its own:
+// with both walks in one, the loop's scalars spill and a pass of the nearest
+// separations takes 5 % longer).
+template <int C, bool TABLE, bool FAR>
 __device__ __forceinline__ void exchange_all_staged(
     const LigDev& L, uint64_t sweep, int max_sep, int n_sub, uint64_t seed,
     XStage& X, double* em) {
@@ -320,23 +380,27 @@ __device__ __forceinline__ void exchange_all_staged(
   const bool act = a < K;
   double ua[C1];
   staged_load<C>(X.sw + (act ? a : 0) * C1, ua);
-  for (int j = 0; j < n_sub; ++j) {
-    for (int d = 1; d <= dmax; ++d) {
-      const int* ros = X.ros[cur];
-      double2* el = X.el[lb];
-      // energies of the state's replica at the half's states, the energy at
-      // the state of its own (h = 0) or the next state's replica (h = 1)
-      double e[kXHalf + 1], be[kXHalf + 1];
-      int st[kXHalf + 1];
-      if (act) {
-        const int r = ros[a], r1 = ros[a + d < K ? a + d : a];
-        double v[C1], v1[C1];
-        if (!TABLE) {
-          staged_load<C>(X.cp + r * C1, v);
-          if (h == 1) staged_load<C>(X.cp + r1 * C1, v1);
-        }
+  // S steps of each half, or (BOTH false) of the first only
+  auto ahead = [&](int d, auto steps, auto halves) {
+    constexpr int S = decltype(steps)::value;
+    constexpr bool BOTH = decltype(halves)::value;
+    const int* ros = X.ros[cur];
+    double2* el = X.el[lb];
+    const bool mine = act && (BOTH || h == 0);
+    // energies of the state's replica at the half's states, the energy at
+    // the state of its own (h = 0) or the next state's replica (h = 1)
+    double e[S + 1], be[S + 1];
+    int st[S + 1];
+    if (act) {
+      const int r = ros[a], r1 = ros[a + d < K ? a + d : a];
+      double v[C1], v1[C1];
+      if (!TABLE) {
+        staged_load<C>(X.cp + r * C1, v);
+        if (h == 1) staged_load<C>(X.cp + r1 * C1, v1);
+      }
+      if (mine) {
 #pragma unroll
-        for (int m = 0; m <= kXHalf; ++m) {
+        for (int m = 0; m <= S; ++m) {
           const int s = a + (kXHalf * h + m) * d;
           st[m] = s < K ? s : a;  // past the end: any state (not counted)
           double u[C1];
@@ -344,34 +408,57 @@ __device__ __forceinline__ void exchange_all_staged(
           e[m] = TABLE ? em[st[m] * kXTable + r] : staged_sum<C>(v, u);
           be[m] = u[C];
         }
-        if (h == 0) {
-          X.ecur[a] = e[0];
-        } else {
-          el[a].x = TABLE ? em[a * kXTable + r1] : staged_sum<C>(v1, ua);
-        }
       }
-      __syncthreads();
-      if (act) {
-        int len = 0;
-        bool go = true;
+      if (h == 0) {
+        X.ecur[a] = e[0];
+      } else {
+        el[a].x = TABLE ? em[a * kXTable + r1] : staged_sum<C>(v1, ua);
+      }
+    }
+    __syncthreads();
+    if (mine) {
+      int len = 0;
+      bool go = true;
 #pragma unroll
-        for (int m = 0; m < kXHalf; ++m) {
-          const bool ok = staged_accepts(be[m], be[m + 1], el[st[m]], e[m],
-                                         e[m + 1], X.ecur[st[m + 1]]);
-          go = (bool)(go & ok & (a + (kXHalf * h + m + 1) * d < K));
-          len += go ? 1 : 0;
-        }
-        X.len[h][a] = len;
+      for (int m = 0; m < S; ++m) {
+        const bool ok = staged_accepts(be[m], be[m + 1], el[st[m]], e[m],
+                                       e[m + 1], X.ecur[st[m + 1]]);
+        go = (bool)(go & ok & (a + (kXHalf * h + m + 1) * d < K));
+        len += go ? 1 : 0;
       }
-      __syncthreads();
-      // (3) the walk; the next pass's uniforms by the wavefronts without a
-      // class meanwhile (by every one, first, when all have classes)
+      X.len[h][a] = len;
+    } else if (act) {
+      X.len[h][a] = 0;
+    }
+    __syncthreads();
+  };
+  using std::integral_constant;
+  using both = std::true_type;
+  const int dw = exchange_wave_separations(K);
+  for (int j = 0; j < n_sub; ++j) {
+    for (int d = 1; d <= dmax; ++d) {
+      const bool lanes = FAR && d > dw;
+      // two positions a class, as most separations of a whole ladder have,
+      // or as many as the first half's steps reach
+      if (FAR && 2 * d >= K)
+        ahead(d, integral_constant<int, 1>{}, std::false_type{});
+      else if (FAR && (kXHalf + 1) * d >= K)
+        ahead(d, integral_constant<int, kXHalf>{}, std::false_type{});
+      else
+        ahead(d, integral_constant<int, kXHalf>{}, both{});
+      // (3) the walk, a wavefront or a lane per class; the next pass's
+      // uniforms by the wavefronts without a class meanwhile (by every one,
+      // first, when all have classes)
       const int dn = d < dmax ? d + 1 : 1, jn = d < dmax ? j : j + 1;
-      const int w0 = d < nw ? d : 0;
+      const int w0 = lanes ? (d + kWave - 1) / kWave : d < nw ? d : 0;
       if (jn < n_sub && wv >= w0)
         draw_pass(jn, dn, lb ^ 1, tid - w0 * kWave, nt - w0 * kWave);
-      for (int rho = wv; rho < d; rho += nw)
-        exchange_class<C, TABLE>(X, em, K, d, rho, cur, lb, d == 1);
+      if (!lanes) {
+        for (int rho = wv; rho < d; rho += nw)
+          exchange_class<C, TABLE>(X, em, K, d, rho, cur, lb, d == 1);
+      } else if (tid < d) {
+        exchange_lane<C, TABLE>(X, em, K, d, tid, cur, lb);
+      }
       cur ^= 1;
       lb ^= 1;
       __syncthreads();
@@ -393,6 +480,7 @@ __device__ __forceinline__ void exchange_all_staged(
 // exchange sweeps in a row, sweep j drawing its uniforms with replica field j
 // Inlined into its kernels, with everything below it: in a called function
 // the staged data's pointers are generic and every access a flat one.
+template <bool FAR>
 __device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
                                                int scheme, int max_sep,
                                                int n_sub, uint64_t seed) {
@@ -409,13 +497,17 @@ __device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
         attempt_pair(L, a, a + 1, 1, sweep, j, seed);
     }
   } else if (K <= kXTable && L.C == 3) {
-    exchange_all_staged<3, true>(L, sweep, max_sep, n_sub, seed, X, em);
+    exchange_all_staged<3, true, FAR>(L, sweep, max_sep, n_sub, seed, X,
+                                      em);
   } else if (K <= kXTable && L.C == 5) {
-    exchange_all_staged<5, true>(L, sweep, max_sep, n_sub, seed, X, em);
+    exchange_all_staged<5, true, FAR>(L, sweep, max_sep, n_sub, seed, X,
+                                      em);
   } else if (K <= kXStates && L.C == 3) {
-    exchange_all_staged<3, false>(L, sweep, max_sep, n_sub, seed, X, em);
+    exchange_all_staged<3, false, FAR>(L, sweep, max_sep, n_sub, seed, X,
+                                      em);
   } else if (K <= kXStates && L.C == 5) {
-    exchange_all_staged<5, false>(L, sweep, max_sep, n_sub, seed, X, em);
+    exchange_all_staged<5, false, FAR>(L, sweep, max_sep, n_sub, seed, X,
+                                      em);
   } else if (threadIdx.x == 0) {
     const int dmax = max_sep < K - 1 ? max_sep : K - 1;
     for (int j = 0; j < n_sub; ++j)
@@ -431,12 +523,13 @@ __device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
 
 // Tail of one ligand's sweep, run by one whole block: exchange (if due),
 // record one sample per state (if due), counter += 1.
+template <bool FAR>
 __device__ __forceinline__ void sweep_tail(const LigDev& L, int exchange_every,
                                            int scheme, int max_sep, int n_sub,
                                            int sample_every, uint64_t seed) {
   const unsigned long long s = *L.counter;
   if (exchange_every > 0 && s % (unsigned long long)exchange_every == 0ull)
-    exchange_block(L, s, scheme, max_sep, n_sub, seed);
+    exchange_block<FAR>(L, s, scheme, max_sep, n_sub, seed);
   __syncthreads();
   const unsigned long long rec = *L.n_rec;
   const bool record = sample_every > 0 &&
@@ -463,10 +556,11 @@ __device__ __forceinline__ void sweep_tail(const LigDev& L, int exchange_every,
 }
 
 // One block per ligand: the tail as a kernel of its own.
+template <bool FAR>
 __global__ __launch_bounds__(kXThreads) void k_sweep_tail(
     const LigDev* __restrict__ ligs, int exchange_every, int scheme,
     int max_sep, int n_sub, int sample_every, uint64_t seed) {
-  sweep_tail(ligs[blockIdx.x], exchange_every, scheme, max_sep, n_sub,
+  sweep_tail<FAR>(ligs[blockIdx.x], exchange_every, scheme, max_sep, n_sub,
              sample_every, seed);
 }
 
@@ -792,11 +886,12 @@ __global__ __launch_bounds__(W * kWave) void k_hmc_sweep(
   }
 }
 
+template <bool FAR>
 __global__ __launch_bounds__(kXThreads) void k_exchange(
     const LigDev* __restrict__ ligs, int scheme, int max_sep, int n_sub,
     uint64_t seed) {
   const LigDev& L = ligs[blockIdx.x];
-  exchange_block(L, *L.counter, scheme, max_sep, n_sub, seed);
+  exchange_block<FAR>(L, *L.counter, scheme, max_sep, n_sub, seed);
 }
 
 // ----------------------------------------------------------------------------
@@ -1409,10 +1504,11 @@ hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
 
 hipError_t launch_sweep_tail(const LigDev* d_ligs, int n_ligs,
                              int exchange_every, int scheme, int max_sep,
-                             int n_sub, int sample_every, uint64_t seed,
-                             hipStream_t st) {
+                             int n_sub, int sample_every, bool far,
+                             uint64_t seed, hipStream_t st) {
   if (n_ligs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sweep_tail, dim3(n_ligs), dim3(kXThreads), 0, st, d_ligs,
+  hipLaunchKernelGGL(far ? k_sweep_tail<true> : k_sweep_tail<false>,
+                     dim3(n_ligs), dim3(kXThreads), 0, st, d_ligs,
                      exchange_every, scheme, max_sep, n_sub, sample_every,
                      seed);
   return hipGetLastError();
@@ -1435,11 +1531,12 @@ hipError_t launch_sweep_finish(const LigDev* d_ligs, int n_ligs,
 }
 
 hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
-                           int max_sep, int n_sub, uint64_t seed,
+                           int max_sep, int n_sub, bool far, uint64_t seed,
                            hipStream_t st) {
   if (n_ligs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_exchange, dim3(n_ligs), dim3(kXThreads), 0, st, d_lig,
-                     scheme, max_sep, n_sub, seed);
+  hipLaunchKernelGGL(far ? k_exchange<true> : k_exchange<false>, dim3(n_ligs),
+                     dim3(kXThreads), 0, st, d_lig, scheme, max_sep, n_sub,
+                     seed);
   return hipGetLastError();
 }
 

@@ -252,6 +252,61 @@ def test_exchange_walk_block_edges(K, C, max_sep, scale):
     ctx.close()
 
 
+@pytest.mark.parametrize("K,C,max_sep", [
+    (10, 3, 300), (17, 5, 16), (64, 3, 9), (65, 3, 17), (73, 5, 18),
+    (163, 3, 40), (192, 5, 17), (193, 3, 25), (255, 5, 254)])
+@pytest.mark.parametrize("scale", [0.02, 0.6, 6.0])
+def test_exchange_far_separations(K, C, max_sep, scale):
+    """All-separation sweeps past the separations that are walked by a
+    wavefront per class: classes of one to twenty states walked by a lane
+    each, runs that end at once and runs that go past the steps decided
+    ahead.  Labels and counts equal the oracle's."""
+    print_case("exchange far", K, C, max_sep, scale)
+    g, lig = _exchange_ligand(K, C)
+    rng = np.random.default_rng([3, K, C, int(100 * scale)])
+    comps = rng.normal(scale=scale, size=(K, 1 + C))
+    sor = rng.permutation(K).astype(np.int32)
+    ctx, (lid,) = make_context(g, [lig], seed=31)
+    ctx.set_replicas(lid, lig.x0, sor, comps, 8)
+    ctx.exchange(lid, scheme=1, max_sep=max_sep, n_sweeps=3)
+    st = ctx.get_replicas(lid)
+    s = oracle.Sampler(oracle.OGrid(g), oracle.OLigand(lig), seed=31,
+                       lig_id=lid, x0=lig.x0)
+    s.comps = np.ascontiguousarray(comps)
+    s.state = sor.copy()
+    s.rep_of_state = np.ascontiguousarray(np.argsort(sor).astype(np.int32))
+    s.sweep_count = 8
+    s.exchange(scheme=1, max_sep=max_sep, n_sweeps=3)
+    assert np.array_equal(st["state_of_replica"], s.state)
+    stats = ctx.get_stats(lid)
+    assert np.array_equal(stats["ex_try"], s.ex_try)
+    assert np.array_equal(stats["ex_acc"], s.ex_acc)
+    ctx.close()
+
+
+def test_exchange_far_separations_cost_no_more_than_near_ones():
+    """A separation with many short classes is not dearer than one with few
+    long ones (a wavefront for each of them, eight at a time, made it five
+    times as dear): time a separation over all 255 of 256 states, against
+    twice the time a separation over the nearest five."""
+    print_case("exchange far time")
+    g, lig = _exchange_ligand(256, 3)
+    ctx, (lid,) = make_context(g, [lig], seed=37)
+
+    def us(max_sep, n_sweeps):
+        best = float("inf")
+        for _ in range(10):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            ctx.exchange(lid, scheme=1, max_sep=max_sep, n_sweeps=n_sweeps)
+            b.record()
+            b.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b))
+        return best / (max_sep * n_sweeps)
+    assert us(255, 1) < 2 * us(5, 25)
+    ctx.close()
+
+
 def test_checkpoint_resume_is_bitwise():
     print_case("checkpoint")
     system = synth.make_system(1)
