@@ -84,10 +84,10 @@ struct LigHost {
   // place in the batched pose-move tables (build_pose_tables): first task
   // (= first row), first forward group and their count
   int ptask0 = -1, pgroup0 = 0, n_pgroups = 0;
-  // bf16 copies of the weights (kTSize), stale while wt_dirty (after the fp32
-  // parameters change; training keeps them up to date)
+  // bf16 copies of the weights (kTSize), written on the stream whenever the
+  // fp32 parameters are (setup, proposal_params, training), so that no call,
+  // eager or replayed from a captured graph, has to know of a change
   unsigned short* wt = nullptr;
-  bool wt_dirty = true;
   // intramolecular nonbonded / implicit-solvent terms (bpmf_pair_setup)
   bool has_pairs = false;
   void* pair_arena = nullptr;
@@ -935,7 +935,6 @@ namespace {
 // the batched pose moves' network outputs
 int pose_scratch(bpmf_ctx* c);
 int build_pose_tables(bpmf_ctx* c);
-int refresh_pose_weights(bpmf_ctx* c);
 int pair_sample_refresh(bpmf_ctx* c, int lid);
 // closing a unit of neighbour-scheme sweeps inside the pose-move launches:
 // the ligands [l0, l1) whose run ends there and the run's parameters
@@ -1151,7 +1150,7 @@ static int hmc_sweep_impl(bpmf_ctx* c, const bpmf_sweep_args* a, int only) {
     // units of P sweeps, each followed by the unit's moves; the network's
     // scratch is sized before any capture
     if (a->pose_move_every > 0) {
-      if ((rc = build_pose_tables(c)) || (rc = refresh_pose_weights(c)))
+      if ((rc = build_pose_tables(c)))
         return rc;
       if (c->n_ptasks > 0 && (rc = pose_scratch(c))) return rc;
     }
@@ -2339,14 +2338,6 @@ int train_scratch(bpmf_ctx* c, int B, int steps, TrainArgs* t, float** split,
   return BPMF_OK;
 }
 
-// the ligand's bf16 weight copies, when its fp32 parameters have changed
-int refresh_weights(bpmf_ctx* c, LigHost& h) {
-  if (!h.wt_dirty) return BPMF_OK;
-  HIP_TRY(launch_weights_bf16(h.params, h.wt, c->stream));
-  h.wt_dirty = false;
-  return BPMF_OK;
-}
-
 int check_prop(bpmf_ctx* c, int lid) {
   int rc = check_lig(c, lid);
   if (rc) return rc;
@@ -2411,6 +2402,9 @@ extern "C" int bpmf_proposal_setup(bpmf_ctx* c, int lid, const int* frame_atoms,
   if (e == hipSuccess)
     e = hipMemcpyAsync(base + o_dev, &pd, sizeof(PropDev), hipMemcpyHostToDevice,
                        c->stream);
+  if (e == hipSuccess)
+    e = launch_weights_bf16((float*)(base + o_p),
+                            (unsigned short*)(base + o_wt), c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
     c->dfree(base);
@@ -2423,7 +2417,6 @@ extern "C" int bpmf_proposal_setup(bpmf_ctx* c, int lid, const int* frame_atoms,
   h.adam_v = (float*)(base + o_v);
   h.d_prop = (PropDev*)(base + o_dev);
   h.wt = (unsigned short*)(base + o_wt);
-  h.wt_dirty = true;
   h.prop = pd;
   h.adam_t = 0;
   h.has_prop = true;
@@ -2440,7 +2433,7 @@ extern "C" int bpmf_proposal_params(bpmf_ctx* c, int lid, float* out,
   if (in) {
     HIP_TRY(hipMemcpyAsync(h.params, in, kNParams * 4, hipMemcpyHostToDevice,
                            c->stream));
-    h.wt_dirty = true;
+    HIP_TRY(launch_weights_bf16(h.params, h.wt, c->stream));
   }
   if (out)
     HIP_TRY(hipMemcpyAsync(out, h.params, kNParams * 4, hipMemcpyDeviceToHost,
@@ -2475,7 +2468,6 @@ extern "C" int bpmf_proposal_forward(bpmf_ctx* c, int lid,
   if (N == 0) return BPMF_OK;
   if (!dev_feats || !dev_out) return fail(BPMF_E_INVAL, "null argument");
   LigHost& h = c->ligs[lid];
-  if ((rc = refresh_weights(c, h))) return rc;
   HIP_TRY(launch_mlp_forward(h.params, h.wt, dev_feats, (int)N, dev_out,
                              c->stream));
   return BPMF_OK;
@@ -2491,7 +2483,6 @@ extern "C" int bpmf_proposal_grad(bpmf_ctx* c, int lid, const float* dev_feats,
   if (!dev_feats || !dev_poses || !dev_grad)
     return fail(BPMF_E_INVAL, "null argument");
   LigHost& h = c->ligs[lid];
-  if ((rc = refresh_weights(c, h))) return rc;
   TrainArgs t{};
   float* split;
   double* d_loss;
@@ -2524,7 +2515,6 @@ extern "C" int bpmf_proposal_train(bpmf_ctx* c, int lid, const float* dev_feats,
   if (!dev_feats || !dev_poses) return fail(BPMF_E_INVAL, "null data");
   if (steps == 0) return BPMF_OK;
   LigHost& h = c->ligs[lid];
-  if ((rc = refresh_weights(c, h))) return rc;
   // the losses of up to kLossSteps steps are read back together
   constexpr int kLossSteps = 1024;
   TrainArgs t{};
@@ -2633,24 +2623,10 @@ int build_pose_tables(bpmf_ctx* c) {
   return BPMF_OK;
 }
 
-// Refresh the bf16 weight copies that are stale (enqueued on the stream;
-// called outside graph capture, before the moves that read them).
-int refresh_pose_weights(bpmf_ctx* c) {
-  for (auto& h : c->ligs)
-    if (h.has_prop) {
-      const int rc = refresh_weights(c, h);
-      if (rc) return rc;
-    }
-  return BPMF_OK;
-}
-
-// One pose move of every replica of ligand `only` (-1: of every ligand
-// with a proposal): features, the network and the move, each one launch
-// over all of the ligands (the move one per wavefront class).  The tables
-// and the network's scratch must be ready (not rebuilt under capture).
 // One pose move of every replica of every ligand with a proposal (or of
 // ligand `only`): the network on the current configurations, then the
-// moves.  close: the run of sweeps before it ends in the network launch
+// moves.  The tables and the network's scratch must be ready (not rebuilt
+// under capture).  close: the run of sweeps before it ends in the network launch
 // (its extra blocks apply the last exchange and record of ligands
 // [l0, l1)) and the next one starts in the move launch, so that no begin or
 // finish kernel brackets the unit; every ligand in that range must have a
@@ -2698,7 +2674,7 @@ extern "C" int bpmf_pose_move(bpmf_ctx* c, int lid, int rounds) {
   if (rc) return rc;
   if (rounds < 0) return fail(BPMF_E_INVAL, "negative rounds");
   if (lid != -1 && (rc = check_prop(c, lid))) return rc;
-  if ((rc = build_pose_tables(c)) || (rc = refresh_pose_weights(c))) return rc;
+  if ((rc = build_pose_tables(c))) return rc;
   for (int r = 0; r < rounds; ++r)
     if ((rc = pose_move_batch(c, lid, c->stream))) return rc;
   return BPMF_OK;

@@ -120,6 +120,63 @@ def test_gradients_match_oracle():
     ctx.close()
 
 
+def test_captured_network_follows_the_parameters():
+    """A forward pass captured in a graph gives the outputs of the parameters
+    set since, replay after replay, and capturing one leaves nothing stale
+    for the calls after it: the parameters as set, after training, and set
+    anew, with the eager pass of a context of its own as the reference."""
+    print_case("captured forward")
+    system, lig = _ligand("c1")
+    g = system.grid
+    rng = np.random.default_rng(8)
+    nets = [flat(Lr.init_weights(np.random.default_rng(s)))
+            for s in (1, 2, 3)]
+    feats = dev(np.sin(rng.uniform(-3, 3, size=(37, 16))), torch.float32)
+    poses = dev(rng.normal(size=(37, 6)), torch.float32)
+
+    def eager(net):
+        ref, (l,) = make_context(g, [lig], seed=5)
+        ref.proposal_setup(l, lig.frame_atoms, lig.tors[lig.cond_tors], net)
+        out = ref.proposal_forward(l, feats).clone()
+        torch.cuda.synchronize()
+        ref.close()
+        return out
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    import paper_1507_03703_amd as pkg
+    with torch.cuda.stream(side):
+        ctx = pkg.Context(seed=5, device=0, stream=side)
+        ctx.grid_upload(g.nodes, g.origin, g.spacing, g.transform)
+        lid = ctx.ligand_setup(lig)
+        ctx.proposal_setup(lid, lig.frame_atoms, lig.tors[lig.cond_tors],
+                           nets[0])
+        ctx.proposal_forward(lid, feats)
+        ctx.proposal_train(lid, feats, poses, batch=32, steps=1, lr=1e-3)
+        ctx.proposal_params(lid, new=nets[1])
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            out = ctx.proposal_forward(lid, feats)
+        # the capture itself has run nothing
+        got = ctx.proposal_forward(lid, feats).clone()
+        side.synchronize()
+        assert torch.equal(got, eager(nets[1]))
+        for net in (nets[1], nets[2], nets[0], None, nets[1]):
+            if net is None:
+                ctx.proposal_train(lid, feats, poses, batch=32, steps=3,
+                                   lr=1e-2)
+                net = ctx.proposal_params(lid)
+            else:
+                ctx.proposal_params(lid, new=net)
+            graph.replay()
+            got = out.clone()
+            side.synchronize()
+            want = eager(net)
+            assert torch.equal(got, want)
+            assert torch.equal(ctx.proposal_forward(lid, feats), want)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B", [1, 15, 16, 17, 32, 33, 4096, 4097])
 def test_training_row_and_split_edges(B):
     """Batches around the 16-row blocks, the 32-row chunks and the first split
