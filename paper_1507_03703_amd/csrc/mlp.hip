@@ -1263,9 +1263,15 @@ hipError_t launch_pose_features(const LigDev* lig, const PropDev* prop, int n,
                                 float* poses, hipStream_t st) {
   if (N <= 0) return hipSuccess;
   const int m = feat_confs(n);
-  hipLaunchKernelGGL(k_pose_features, dim3((unsigned)((N + m - 1) / m)),
-                     dim3(kFeatWaves * 64), m * feat_row(n) * 4, st, lig, prop,
-                     xs, N, feats, poses);
+  // a launch's share: a grid of 2^32 threads or more is cut short silently
+  const int64_t most = ((1ll << 24) - 1) * m;
+  for (int64_t c = 0; c < N; c += most) {
+    const int64_t now = N - c < most ? N - c : most;
+    hipLaunchKernelGGL(k_pose_features, dim3((unsigned)((now + m - 1) / m)),
+                       dim3(kFeatWaves * 64), m * feat_row(n) * 4, st, lig,
+                       prop, xs + c * n * 3, now, feats + c * kNFeat,
+                       poses + c * 6);
+  }
   return hipGetLastError();
 }
 

@@ -284,6 +284,34 @@ def test_pose_features_block_edges(which, N):
     ctx.close()
 
 
+def test_pose_features_past_one_launch():
+    """More configurations than one launch has threads for (2^32, four a
+    configuration): rows on both sides of where a launch ends, and the last
+    ones, have the bits of a call with those rows alone."""
+    N = (1 << 30) + 100
+    print_case("pose_features past one launch", N)
+    if torch.cuda.mem_get_info()[0] < 150e9:
+        pytest.skip("needs 133 GB of device memory")
+    system, _ = _ligand("c1")
+    lig = synth.make_ligand(np.random.default_rng(4), 3, 2)
+    ctx, (lid,) = make_context(system.grid, [lig], seed=1)
+    ctx.proposal_setup(lid, [0, 1, 2], np.zeros((0, 4), np.int32),
+                       flat(Lr.init_weights(np.random.default_rng(1))))
+    x = torch.zeros((N, 3, 3), dtype=torch.float32, device="cuda:0")
+    rows = [slice(0, 70), slice((1 << 30) - 140, (1 << 30) + 100)]
+    rng = np.random.default_rng(2)
+    for r in rows:
+        x[r] = dev(rng.normal(size=(r.stop - r.start, 3, 3)), torch.float32)
+    f, p = ctx.pose_features(lid, x)
+    for r in rows:
+        fr, pr = ctx.pose_features(lid, x[r].clone())
+        assert torch.equal(f[r], fr)
+        assert torch.equal(p[r], pr)
+    ctx.close()
+    del x, f, p
+    torch.cuda.empty_cache()
+
+
 def _check_pose_moves(ctx, og, lig, lid, seed, rounds, sweeps=2):
     """`rounds` times: a few sweeps of every ligand, then one pose move of
     every ligand with a proposal (ligand -1), checked replica by replica on
