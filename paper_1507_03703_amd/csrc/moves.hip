@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "device.h"
 #include "internal.h"
 #include "moves.h"
@@ -332,8 +334,8 @@ namespace bpmf {
 
 namespace {
 
-// kPlacePoses consecutive poses per workgroup.  A pose's site position and
-// rotation (double: a cube root, three sine-cosine pairs) and its
+// `per` consecutive poses (up to kPlacePoses) per workgroup.  A pose's site
+// position and rotation (double: a cube root, three sine-cosine pairs) and its
 // configuration's centre of mass are worked out once, by one thread each, and
 // used for all its atoms, one thread per atom; the coordinates pass through
 // LDS so that they leave 16 bytes at a time.  225000 poses of 24 atoms (65
@@ -346,13 +348,14 @@ struct PlacedPose {
 };
 __global__ __launch_bounds__(kPlaceThreads) void k_place_poses(
     const LigDev* __restrict__ lig, const float* __restrict__ confs,
-    int n_com, int n_orient, int64_t first, int64_t count, uint64_t seed, float* __restrict__ out) {
+    int n_com, int n_orient, int64_t first, int64_t count, int per,
+    uint64_t seed, float* __restrict__ out) {
   __shared__ PlacedPose s_p[kPlacePoses];
   __shared__ __align__(16) float s_x[kPlaceThreads * 3];
   const LigDev& L = *lig;
   const int n = L.n, tid = threadIdx.x, lane = tid & 63;
-  const int64_t p0 = (int64_t)blockIdx.x * kPlacePoses;
-  const int m = (int)(count - p0 < kPlacePoses ? count - p0 : kPlacePoses);
+  const int64_t p0 = (int64_t)blockIdx.x * per;
+  const int m = (int)(count - p0 < per ? count - p0 : per);
   static_assert(kPlacePoses == 64, "a wavefront for each part of a pose");
   if (lane < m) {
     const int64_t p = first + p0 + lane;
@@ -445,15 +448,21 @@ hipError_t launch_place_poses(const LigDev* lig, int n, const float* confs,
                               int64_t count, uint64_t seed, float* out,
                               hipStream_t st) {
   if (count <= 0) return hipSuccess;
-  // the most atoms one call places (2^32 threads, one an atom)
+  // the most atoms one call places: 2^32, less a few hundred
   if ((count * n + 255) / 256 > (1ll << 24) - 1) return hipErrorInvalidValue;
-  constexpr int64_t kMost = ((1ll << 24) - 1) * kPlacePoses;  // a launch's
-  for (int64_t done = 0; done < count; done += kMost) {
-    const int64_t now = count - done < kMost ? count - done : kMost;
-    hipLaunchKernelGGL(k_place_poses,
-                       dim3((unsigned)((now + kPlacePoses - 1) / kPlacePoses)),
+  // poses a workgroup: 64, or as few as 8 (a multiple of 4: 16-byte stores)
+  // where that would leave compute units without one, since a workgroup goes
+  // through its atoms 256 at a time (105 poses of 128 atoms, a call with its
+  // wait: 33 us with 64 to a workgroup, 23 us with 8)
+  const int per = (int)std::min<int64_t>(
+      kPlacePoses, std::max<int64_t>(8, (count + 1023) / 1024 * 4));
+  const int64_t most = ((1ll << 24) - 1) * per;  // a launch's
+  for (int64_t done = 0; done < count; done += most) {
+    const int64_t now = std::min(count - done, most);
+    hipLaunchKernelGGL(k_place_poses, dim3((unsigned)((now + per - 1) / per)),
                        dim3(kPlaceThreads), 0, st, lig, confs, n_com,
-                       n_orient, first + done, now, seed, out + done * n * 3);
+                       n_orient, first + done, now, per, seed,
+                       out + done * n * 3);
   }
   return hipGetLastError();
 }

@@ -191,6 +191,59 @@ def test_placements_block_edges(confs, coms, orients, first, count):
     ctx.close()
 
 
+@pytest.mark.parametrize("confs,coms,orients,first,count",
+                         [(7, 1, 293, 0, 2048), (7, 1, 293, 2, 2049),
+                          (7, 1, 440, 1, 3073), (16, 31, 31, 9, 15360),
+                          (16, 31, 31, 0, 15361)])
+def test_placements_poses_per_workgroup(confs, coms, orients, first, count):
+    """Counts on both sides of where a workgroup takes more poses: 8 to 2048
+    poses, then 12, up to 64 from 15361 on."""
+    print_case(f"placement shares {confs} {coms} {orients} {first} {count}")
+    system = synth.make_system(1)
+    lig, g = system.ligands[0], system.grid
+    ctx, (lid,) = make_context(g, [lig], seed=79)
+    rng = np.random.default_rng(count)
+    x = np.asarray(lig.x0[0] + rng.normal(scale=0.3, size=(
+        confs, lig.n_atoms, 3)), np.float32)
+    ref = P.placements(x.astype(np.float64),
+                       lig.mass.astype(np.float32).astype(np.float64),
+                       np.asarray(lig.site_center, np.float32),
+                       np.float32(lig.d0), coms, orients, seed=79, lig=lid)
+    got = ctx.place_poses(lid, dev(x, torch.float32), coms, orients,
+                          first=first, count=count)
+    assert np.abs(got.cpu().numpy() - ref[first:first + count]).max() < 2e-5
+    ctx.close()
+
+
+def test_a_few_placements_are_spread_over_the_device():
+    """A hundred poses of the largest ligand take little longer than one: a
+    workgroup that places 64 of them, 256 atoms at a time, takes more than
+    twice as long as one pose's."""
+    print_case("placements of a few poses")
+    lig = synth.make_ligand(np.random.default_rng(3), 128, 2, box=9.0)
+    system = synth.make_system(1)
+    ctx, (lid,) = make_context(system.grid, [lig], seed=80)
+    x = dev(np.repeat(lig.x0[:1], 128, axis=0), torch.float32)
+
+    def us(count):
+        out = torch.empty((count, 128, 3), device="cuda:0")
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            torch.cuda._sleep(2000000)  # the calls queue up behind it
+            a.record()
+            for _ in range(50):
+                ctx.place_poses(lid, x, 1, 1, count=count, out=out)
+            b.record()
+            b.synchronize()
+            best = min(best, 20.0 * a.elapsed_time(b))
+        return best
+    one, many = us(1), us(128)
+    print_case(f"placements: 1 pose {one:.1f} us, 128 poses {many:.1f} us")
+    assert many < 1.8 * one
+    ctx.close()
+
+
 def _init_system(n_seeds, capacity):
     system = synth.make_system(1)
     g, (lig,) = synth.add_soft_grids(system.grid, system.ligands[:1])
