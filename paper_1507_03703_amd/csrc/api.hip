@@ -1291,6 +1291,7 @@ struct UknPlan {
   bool pairs[bpmf_ctx::kWaveClasses] = {false, false, false, false};
   // one wavefront per sample (k_energy_matrix_wave) and its LDS
   bool per_wave[bpmf_ctx::kWaveClasses] = {false, false, false, false};
+  int at_once[bpmf_ctx::kWaveClasses] = {};
   int wave_lds[bpmf_ctx::kWaveClasses] = {0, 0, 0, 0};
 };
 
@@ -1390,9 +1391,11 @@ int ukn_plan(bpmf_ctx* c, int n, const int* ligand_ids,
     const int W = 1 << q;
     p->off[q] = nj;
     int64_t first = 0, cfirst = 0;
+    bool one = false, two = false;
     for (int i = 0; i < n; ++i) {
       const LigHost& h = c->ligs[ligand_ids[i]];
       if (class_waves(h) != W || n_samples[i] == 0) continue;
+      (ukn_two_samples(h.dev.n) ? two : one) = true;
       UknJob J;
       J.lig = ligand_ids[i];
       J.cost = ukn_sample_cost(h.dev, h.min_waves);
@@ -1416,6 +1419,7 @@ int ukn_plan(bpmf_ctx* c, int n, const int* ligand_ids,
     // a class whose ligands have no pair terms in their energy and whose
     // per-wavefront LDS fits runs one wavefront per sample
     p->per_wave[q] = W <= 2 && !p->pairs[q] && p->wave_lds[q] <= 65536;
+    p->at_once[q] = one && two ? 0 : two ? 2 : 1;
     p->cnt[q] = nj - p->off[q];
     p->total[q] = first;
     UknJob end{};
@@ -1469,7 +1473,7 @@ int ukn_launch(bpmf_ctx* c, const UknPlan& p, const UknJob* d_jobs,
     HIP_TRY(launch_energy_matrix(
         c->grid, c->d_ligs, 1 << q, d_jobs + p.off[q], p.cnt[q], p.total[q],
         p.group, p.per_wave[q] ? p.wave_lds[q] : p.lds[q], c->n_cu,
-        p.pairs[q], p.per_wave[q], sq));
+        p.pairs[q], p.per_wave[q], p.at_once[q], sq));
     if (fork && i > 0) HIP_TRY(hipEventRecord(c->class_join[q], sq));
   }
   if (fork)

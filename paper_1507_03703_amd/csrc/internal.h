@@ -57,6 +57,8 @@ __host__ __device__ inline int block_lds_bytes(int waves, bool forces, int n,
 // kUknWaveGroup samples, then the ligand's topology (as stage_topology lays
 // it out)
 constexpr int kUknWaves = 4, kUknWaveGroup = 8;
+// a wavefront takes two samples at once
+__host__ __device__ constexpr bool ukn_two_samples(int n) { return n <= 32; }
 __host__ __device__ inline int ukn_wave_head_bytes(int K, int C) {
   return (K * (C + 1) * 8 + 15) & ~15;
 }
@@ -241,12 +243,14 @@ struct UknJob {
 // columns are staged in LDS before they are written.  per_wave: one
 // wavefront per sample (k_energy_matrix_wave, for ligands whose pair terms
 // are not in the energy; `waves` is then the atoms per lane, 1 or 2, and
-// lds_bytes comes from ukn_wave_lds_bytes)
+// lds_bytes comes from ukn_wave_lds_bytes); at_once: samples a wavefront takes
+// at once at one atom per lane, ukn_two_samples of every ligand of the launch
+// (2, 1) or 0 where they differ
 hipError_t launch_energy_matrix(const GridDev& g, const LigDev* d_ligs,
                                 int waves, const UknJob* d_jobs, int n_jobs,
                                 int64_t total, int group, int lds_bytes,
                                 int n_cu, bool pairs, bool per_wave,
-                                hipStream_t st);
+                                int at_once, hipStream_t st);
 // copy n jobs from host memory into the device table dst by kernels that
 // take the jobs as arguments (no host staging buffer, no copy engine)
 hipError_t launch_put_jobs(UknJob* dst, const UknJob* jobs, int n,

@@ -1024,11 +1024,11 @@ __global__ __launch_bounds__(W * kWave) void k_energy_matrix(
 // pair terms are not in the energy.  A block of kUknWaves wavefronts stages
 // the topology of its current job once (shared by its wavefronts); the job's
 // samples are dealt to the wavefronts in runs, worked through in groups of
-// up to kUknWaveGroup.  A wavefront evaluates a sample alone: lane l owns atoms l and l + 64
-// (AP = 2) or l; the grid terms of its atoms, every bonded chunk of the ligand
-// (energies only), the mass-weighted position sums of the restraint, then
-// double sums over the wavefront, as the lean block evaluation forms them:
-// U0 = (bonded total) + U_I, and the C channel sums.  Its LDS (positions, the
+// up to kUknWaveGroup.  A wavefront evaluates a sample alone: lane l owns
+// atoms l and l + 64 (AP = 2) or l; the grid terms of its atoms, every bonded
+// chunk of the ligand (energies only), the mass-weighted position sums of the
+// restraint, then double sums over the wavefront, as the lean block evaluation
+// forms them: U0 = (bonded total) + U_I, and the C channel sums.  Its LDS (positions, the
 // group's columns) is its own; LDS operations of one wavefront complete in
 // order, so its lanes see each other's stores after a wavefront-scope fence.
 //
@@ -1039,7 +1039,10 @@ __global__ __launch_bounds__(W * kWave) void k_energy_matrix(
 // dealt in groups of 8, 133 samples to four wavefronts left one with 40 (32
 // ligands of 10 to 80 atoms, 3200 samples each: 165 -> 135 us, with the
 // halves).  Registers: four wavefronts a SIMD with 3 channels, three with 5
-// (four spill: 230 us instead of 212).
+// (four spill: 230 us instead of 212); both forms in one kernel spill as well,
+// so a launch whose ligands all take the same one has a kernel of that form
+// (one ligand of 48 atoms, 12000 samples of 4 states, a call with its wait:
+// 50.2 us with both in the kernel, 48.2 us).
 // The float sums of a half are those of a whole wavefront with the sample in
 // its lower half: a lane's bonded items 64 apart in one accumulator, the
 // position sums over two rows of 16.
@@ -1230,8 +1233,11 @@ __device__ __forceinline__ void ukn_group(const GridDev& g, const LigDev& L,
   wave_fence();
 }
 
-template <int C, int AP>
-__global__ __launch_bounds__(kUknWaves * kWave, C == 3 ? 4 : 3) void k_energy_matrix_wave(
+// H: samples a wavefront takes at once, 0 by the ligand (launches with ligands
+// on both sides of 32 atoms).
+template <int C, int AP, int H>
+__global__ __launch_bounds__(kUknWaves * kWave, C == 3 ? 4 : 3)
+void k_energy_matrix_wave(
     GridDev g, const LigDev* __restrict__ ligs,
     const UknJob* __restrict__ jobs, int n_jobs, int64_t total) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1263,7 +1269,7 @@ __global__ __launch_bounds__(kUknWaves * kWave, C == 3 ? 4 : 3) void k_energy_ma
       ew[i] = i < K * C ? ((gcdouble*)L.wd)[i]
                         : ((gcdouble*)L.beta)[i - K * C];
     __syncthreads();
-    const bool two = AP == 1 && 2 * n <= kWave;
+    const bool two = H == 2 || (H == 0 && ukn_two_samples(n));
     float m[AP], sc[AP][C];
     bool own[AP];
 #pragma unroll
@@ -1282,14 +1288,16 @@ __global__ __launch_bounds__(kUknWaves * kWave, C == 3 ? 4 : 3) void k_energy_ma
                            ? s + 2 * (pairs * (wv + 1) / kUknWaves) : e;
     for (int64_t q0 = s0; q0 < s1; q0 += kUknWaveGroup) {
       const int64_t q1 = q0 + kUknWaveGroup < s1 ? q0 + kUknWaveGroup : s1;
-      if constexpr (AP == 1) {
+      if constexpr (H != 1) {
         if (two) {
-          ukn_group<C, 1, 2>(g, L, J, sh, ew, pos, col, m, sc, own, q0, q1,
-                             lane);
+          ukn_group<C, AP, 2>(g, L, J, sh, ew, pos, col, m, sc, own, q0, q1,
+                              lane);
           continue;
         }
       }
-      ukn_group<C, AP, 1>(g, L, J, sh, ew, pos, col, m, sc, own, q0, q1, lane);
+      if constexpr (H != 2)
+        ukn_group<C, AP, 1>(g, L, J, sh, ew, pos, col, m, sc, own, q0, q1,
+                            lane);
     }
     s = e;
   }
@@ -1570,13 +1578,16 @@ hipError_t launch_energy_matrix(const GridDev& g, const LigDev* d_ligs,
                                 int waves, const UknJob* d_jobs, int n_jobs,
                                 int64_t total, int group, int lds_bytes,
                                 int n_cu, bool pairs, bool per_wave,
-                                hipStream_t st) {
+                                int at_once, hipStream_t st) {
   if (total <= 0) return hipSuccess;
   if (per_wave) {
     if (waves != 1 && waves != 2) return hipErrorInvalidValue;
+    if (waves == 2) at_once = 1;
     BPMF_DISPATCH_C(g.C, {
-      auto kern = waves == 1 ? k_energy_matrix_wave<C, 1>
-                             : k_energy_matrix_wave<C, 2>;
+      auto kern = waves == 2     ? k_energy_matrix_wave<C, 2, 1>
+                  : at_once == 2 ? k_energy_matrix_wave<C, 1, 2>
+                  : at_once == 1 ? k_energy_matrix_wave<C, 1, 1>
+                                 : k_energy_matrix_wave<C, 1, 0>;
       int per_cu = 0;
       hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &per_cu, kern, kUknWaves * kWave, lds_bytes);

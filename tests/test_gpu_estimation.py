@@ -75,6 +75,24 @@ def test_energy_matrix_wavefront_edges(atoms, N):
     ctx.close()
 
 
+@pytest.mark.parametrize("atoms", [(32, 12, 31), (33, 64, 50), (32, 33, 7),
+                                   (33, 32, 64), (30, 34, 70)])
+def test_energy_matrix_batch_of_either_and_both_sizes(atoms):
+    """Launches whose ligands all take two samples a wavefront, all one, and
+    both kinds (with a larger ligand in another launch): each matrix the bits
+    of the ligand's own call, which is of one kind."""
+    print_case(f"energy_matrix kinds {atoms}")
+    g = synth.make_system(1).grid
+    rng = np.random.default_rng(atoms[0])
+    ligs = [synth.make_ligand(rng, a, 6, box=8.0) for a in atoms]
+    xs = [dev(_samples(l, rng, 37 + 5 * i), torch.float32)
+          for i, l in enumerate(ligs)]
+    ctx, ids = make_context(g, ligs, seed=1)
+    for lid, x, u in zip(ids, xs, ctx.energy_matrix_batch(ids, xs)):
+        assert torch.equal(u, ctx.energy_matrix(lid, x))
+    ctx.close()
+
+
 def test_energy_matrix_full_size_config2_sampled_entries():
     """64 states x 32000 samples (the production u_kn of the 48-atom
     system), checked on 1000 sampled entries against brute force."""
