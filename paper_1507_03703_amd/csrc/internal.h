@@ -215,9 +215,9 @@ hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
 // both cost the same: a wavefront's walk of a class costs 0.7 us however short
 // the class, all lanes' walks together 0.3 to 1 us by its length.  One sweep
 // over every separation, a wavefront for each class and this way: 64 states
-// 244 and 91 us, 170 states 1433 and 264 us, 256 states 3096 and 432 us (549 us
+// 244 and 87 us, 170 states 1433 and 250 us, 256 states 3096 and 418 us (549 us
 // with one lane per first state following its run); up to 12 separations of
-// 16 states, five sweeps: 110 and 92 us; of 256 states: 173 us by wavefronts,
+// 16 states, five sweeps: 110 and 89 us; of 256 states: 173 us by wavefronts,
 // 248 us by lanes.
 __host__ __device__ constexpr int exchange_wave_separations(int K) {
   return K <= 64 ? 8 : K <= 192 ? 16 : 24;

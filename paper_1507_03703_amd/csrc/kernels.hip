@@ -4,8 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include <type_traits>
-
 #include "deferred.h"
 #include "device.h"
 #include "internal.h"
@@ -333,7 +331,8 @@ __device__ __forceinline__ void exchange_lane(XStage& X, const double* em,
 
 // FAR: some separation is past exchange_wave_separations (a kernel of its own:
 // with both walks in one, the loop's scalars spill and a pass of the nearest
-// separations takes 5 % longer).
+// separations takes 5 % longer); steps past the end of every class, whose
+// energies no run asks for, are then left out.
 template <int C, bool TABLE, bool FAR>
 __device__ __forceinline__ void exchange_all_staged(
     const LigDev& L, uint64_t sweep, int max_sep, int n_sub, uint64_t seed,
@@ -377,30 +376,31 @@ __device__ __forceinline__ void exchange_all_staged(
   // tid mod 256, whose weights they keep in registers
   static_assert(kXThreads == 2 * kXStates, "two threads a state");
   const int h = tid / kXStates, a = tid - h * kXStates;
+  const int hu = wv / (kXStates / kWave);  // h, known to be uniform
   const bool act = a < K;
   double ua[C1];
   staged_load<C>(X.sw + (act ? a : 0) * C1, ua);
-  // S steps of each half, or (BOTH false) of the first only
-  auto ahead = [&](int d, auto steps, auto halves) {
-    constexpr int S = decltype(steps)::value;
-    constexpr bool BOTH = decltype(halves)::value;
-    const int* ros = X.ros[cur];
-    double2* el = X.el[lb];
-    const bool mine = act && (BOTH || h == 0);
-    // energies of the state's replica at the half's states, the energy at
-    // the state of its own (h = 0) or the next state's replica (h = 1)
-    double e[S + 1], be[S + 1];
-    int st[S + 1];
-    if (act) {
-      const int r = ros[a], r1 = ros[a + d < K ? a + d : a];
-      double v[C1], v1[C1];
-      if (!TABLE) {
-        staged_load<C>(X.cp + r * C1, v);
-        if (h == 1) staged_load<C>(X.cp + r1 * C1, v1);
-      }
-      if (mine) {
+  const int dw = exchange_wave_separations(K);
+  for (int j = 0; j < n_sub; ++j) {
+    for (int d = 1; d <= dmax; ++d) {
+      const bool lanes = FAR && d > dw;
+      const int* ros = X.ros[cur];
+      double2* el = X.el[lb];
+      // energies of the state's replica at the half's states, the energy at
+      // the state of its own (h = 0) or the next state's replica (h = 1)
+      double e[kXHalf + 1], be[kXHalf + 1];
+      int st[kXHalf + 1];
+      if (act) {
+        const int r = ros[a], r1 = ros[a + d < K ? a + d : a];
+        double v[C1], v1[C1];
+        if (!TABLE) {
+          staged_load<C>(X.cp + r * C1, v);
+          if (h == 1) staged_load<C>(X.cp + r1 * C1, v1);
+        }
 #pragma unroll
-        for (int m = 0; m <= S; ++m) {
+        for (int m = 0; m <= kXHalf; ++m) {
+          // steps past every class's end
+          if (FAR && (kXHalf * hu + m) * d >= K) break;
           const int s = a + (kXHalf * h + m) * d;
           st[m] = s < K ? s : a;  // past the end: any state (not counted)
           double u[C1];
@@ -408,44 +408,27 @@ __device__ __forceinline__ void exchange_all_staged(
           e[m] = TABLE ? em[st[m] * kXTable + r] : staged_sum<C>(v, u);
           be[m] = u[C];
         }
+        if (h == 0) {
+          X.ecur[a] = e[0];
+        } else {
+          el[a].x = TABLE ? em[a * kXTable + r1] : staged_sum<C>(v1, ua);
+        }
       }
-      if (h == 0) {
-        X.ecur[a] = e[0];
-      } else {
-        el[a].x = TABLE ? em[a * kXTable + r1] : staged_sum<C>(v1, ua);
-      }
-    }
-    __syncthreads();
-    if (mine) {
-      int len = 0;
-      bool go = true;
+      __syncthreads();
+      if (act) {
+        int len = 0;
+        bool go = true;
 #pragma unroll
-      for (int m = 0; m < S; ++m) {
-        const bool ok = staged_accepts(be[m], be[m + 1], el[st[m]], e[m],
-                                       e[m + 1], X.ecur[st[m + 1]]);
-        go = (bool)(go & ok & (a + (kXHalf * h + m + 1) * d < K));
-        len += go ? 1 : 0;
+        for (int m = 0; m < kXHalf; ++m) {
+          if (FAR && (kXHalf * hu + m + 1) * d >= K) break;
+          const bool ok = staged_accepts(be[m], be[m + 1], el[st[m]], e[m],
+                                         e[m + 1], X.ecur[st[m + 1]]);
+          go = (bool)(go & ok & (a + (kXHalf * h + m + 1) * d < K));
+          len += go ? 1 : 0;
+        }
+        X.len[h][a] = len;
       }
-      X.len[h][a] = len;
-    } else if (act) {
-      X.len[h][a] = 0;
-    }
-    __syncthreads();
-  };
-  using std::integral_constant;
-  using both = std::true_type;
-  const int dw = exchange_wave_separations(K);
-  for (int j = 0; j < n_sub; ++j) {
-    for (int d = 1; d <= dmax; ++d) {
-      const bool lanes = FAR && d > dw;
-      // two positions a class, as most separations of a whole ladder have,
-      // or as many as the first half's steps reach
-      if (FAR && 2 * d >= K)
-        ahead(d, integral_constant<int, 1>{}, std::false_type{});
-      else if (FAR && (kXHalf + 1) * d >= K)
-        ahead(d, integral_constant<int, kXHalf>{}, std::false_type{});
-      else
-        ahead(d, integral_constant<int, kXHalf>{}, both{});
+      __syncthreads();
       // (3) the walk, a wavefront or a lane per class; the next pass's
       // uniforms by the wavefronts without a class meanwhile (by every one,
       // first, when all have classes)
