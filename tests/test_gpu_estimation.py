@@ -333,3 +333,38 @@ def test_mbar_tile_edges(K, per):
         assert abs(var[-1] / v64 - 1) < 1e-5
     assert 0 < it < 200
     ctx.close()
+
+
+@pytest.mark.parametrize("K,per", [
+    (2, 40), (3, 43), (15, 17), (16, 20), (17, 19), (31, 33), (33, 31),
+    (48, 22), (49, 23), (64, 17), (65, 19), (80, 15), (97, 16), (113, 17),
+    (128, 14)])
+@pytest.mark.parametrize("infinite", [False, True])
+def test_mbar_every_variance_at_tile_edges(K, per, infinite):
+    """The whole diagonal of the in-register inverse around its blocks'
+    edges, and with infinite energies of some samples in foreign states (a
+    clash), in the last state among them, whose energies the lanes past it
+    repeat.  The states overlap, so the Hessian at the oracle's solution is
+    well conditioned and every variance has to be finite: f to 1e-7 kT and
+    the variances to 1e-5 relative, as in the solves above."""
+    print_case("mbar variances", K, per, infinite)
+    rng = np.random.default_rng([7, K, per])
+    u, Nk = _harmonic_problem(rng, K, per, 0.5)
+    if infinite:
+        own = np.repeat(np.arange(K), Nk)
+        hit = rng.random(u.shape) < 0.02
+        hit[-1] |= rng.random(u.shape[1]) < 0.3
+        hit[own, np.arange(u.shape[1])] = False
+        u = np.where(hit, np.inf, u)
+    ctx = __import__("paper_1507_03703_amd").Context(seed=0)
+    f, var, it = ctx.mbar(dev(u, torch.float64), Nk, tol=1e-11, max_iter=200)
+    f64, _, _ = estimators.mbar(u, Nk, tol=1e-12)
+    a = (np.log(Nk) + f64)[:, None] - u
+    W = np.exp(a - np.logaddexp.reduce(a, axis=0))
+    H = (np.diag(W.sum(1)) - W @ W.T)[1:, 1:]
+    assert np.linalg.cond(H) < 1e5
+    want = np.diag(np.linalg.inv(H)) - 1.0 / Nk[1:] - 1.0 / Nk[0]
+    assert np.max(np.abs(f - f64)) < 1e-7 * max(1.0, np.abs(f64).max())
+    assert np.all(np.isfinite(var)) and var[0] == 0.0
+    assert np.allclose(var[1:], want, rtol=1e-5, atol=1e-12)
+    ctx.close()

@@ -233,6 +233,34 @@ def test_training_row_and_split_edges(B):
     ctx.close()
 
 
+@pytest.mark.parametrize("B", [33, 512, 4096, 4097])
+def test_every_training_row_counts_once(B):
+    """One row in B differs from the others: B times the change of the
+    gradient is that row's gradient less one of the others' (each from a
+    call of one row), so a row that is dropped or taken twice shows in full.
+    2 % in L2, the bf16 operands' tolerance of this file; rows at both ends,
+    around the blocks of 16 and 32, and around the middle, where a split of
+    the rows in two would lie."""
+    print_case(f"mlp rows B={B}")
+    rng, system, lig, p, ctx, lid, _ = _setup(9)
+    f = rng.uniform(-1, 1, (2, 16)).astype(np.float32)
+    poses = np.array([[0.3, -0.4, 0.2, 0.1, 0.5, -0.2],
+                      [6.0, -5.0, 7.0, 2.0, -1.5, 2.5]], np.float32)
+
+    def grad(rows):
+        g, _ = ctx.proposal_grad(lid, dev(f[rows], torch.float32),
+                                 dev(poses[rows], torch.float32))
+        return g.cpu().numpy().astype(np.float64)
+    want = grad([1]) - grad([0])
+    base = grad(np.zeros(B, int))
+    mid = (B + 31) // 32 // 2 * 32
+    for r in {0, 15, 16, 31, 32, mid - 1, mid, B // 16 * 16 - 1, B - 1}:
+        rows = np.zeros(B, int)
+        rows[r] = 1
+        assert rel_l2(B * (grad(rows) - base), want) < 2e-2, r
+    ctx.close()
+
+
 @pytest.mark.parametrize("which", ["c1", "wide90", "wide100"])
 def test_pose_features_match_oracle(which):
     print_case("pose features", which)
@@ -281,6 +309,29 @@ def test_pose_features_block_edges(which, N):
         assert torch.equal(f1[0], f[i]) and torch.equal(p1[0], po[i])
         want = Lr.features(xs[i].astype(np.float32).astype(np.float64), cond)
         assert np.allclose(f[i].cpu().numpy(), want, atol=2e-5)
+    ctx.close()
+
+
+@pytest.mark.parametrize("which,N", [("c1", 1), ("c1", 63), ("c1", 130),
+                                     ("wide90", 33)])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_pose_features_into_any_address(which, N, shift):
+    """Results written `shift` floats past a 16-byte address: the values of
+    an aligned call, and nothing before or after them."""
+    print_case(f"pose features into {which} {N} {shift}")
+    rng, system, lig, p, ctx, lid, cond = _setup(3, which)
+    n = len(lig.mass)
+    x = dev(lig.x0[0] + rng.normal(scale=0.2, size=(N, n, 3)), torch.float32)
+    f, po = ctx.pose_features(lid, x)
+    bufs = [torch.full((N * w + 8,), 7.0, device="cuda:0") for w in (16, 6)]
+    views = [b[shift:shift + N * w] for b, w in zip(bufs, (16, 6))]
+    assert all(v.data_ptr() % 16 == 4 * shift for v in views)
+    assert ctx._lib.bpmf_pose_features(ctx._h, lid, x.data_ptr(), N,
+                                       *[v.data_ptr() for v in views]) == 0
+    for b, v, want in zip(bufs, views, (f, po)):
+        assert torch.equal(v, want.reshape(-1))
+        assert torch.all(b[:shift] == 7.0)
+        assert torch.all(b[shift + v.numel():] == 7.0)
     ctx.close()
 
 
