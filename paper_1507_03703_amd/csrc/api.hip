@@ -947,12 +947,15 @@ int pose_move_batch(bpmf_ctx* c, int only, hipStream_t st,
 int external_moves_range(bpmf_ctx* c, int l0, int l1, int n_moves,
                          int k_max, double sigma, hipStream_t st);
 int check_external(int n_moves, int k_max, double sigma);
-// some ladder of ligands [l0, l1) has separations past those a wavefront
-// walks (exchange_wave_separations)
-bool any_far(bpmf_ctx* c, int l0, int l1, int max_sep) {
-  for (int l = l0; l < l1; ++l)
-    if (exchange_far(c->ligs[l].dev.K, max_sep)) return true;
-  return false;
+// the all-separations exchange's kernel for ligands [l0, l1)
+int walk_of(bpmf_ctx* c, int l0, int l1, int max_sep) {
+  int walk = kWalkShort;
+  for (int l = l0; l < l1; ++l) {
+    const int w = exchange_walk(c->ligs[l].dev.K, max_sep);
+    if (w == kWalkFar) return w;
+    if (w == kWalkNear) walk = w;
+  }
+  return walk;
 }
 }  // namespace
 
@@ -1006,7 +1009,8 @@ static int hmc_sweep_impl(bpmf_ctx* c, const bpmf_sweep_args* a, int only) {
   }
   TailArgs tail{a->exchange_every, a->exchange_scheme, a->max_sep,
                 a->sample_every, n_sub};
-  const bool far = tail.scheme == 1 && any_far(c, l0, l1, tail.max_sep);
+  const int walk =
+      tail.scheme == 1 ? walk_of(c, l0, l1, tail.max_sep) : kWalkNear;
   const int nl = l1 - l0;
   const LigDev* dl = c->d_ligs + l0;  // table entries of the call's ligands
   // scheme 0: each sweep applies the previous one's exchange and record in
@@ -1067,7 +1071,7 @@ static int hmc_sweep_impl(bpmf_ctx* c, const bpmf_sweep_args* a, int only) {
     }
     if (tail.scheme == 1)
       HIP_TRY(launch_sweep_tail(dl, nl, tail.exchange_every, tail.scheme,
-                                tail.max_sep, n_sub, tail.sample_every, far,
+                                tail.max_sep, n_sub, tail.sample_every, walk,
                                 c->seed, st));
     return BPMF_OK;
   };
@@ -1267,8 +1271,8 @@ extern "C" int bpmf_exchange(bpmf_ctx* c, int ligand_id, int scheme,
   const int l0 = ligand_id == -1 ? 0 : ligand_id;
   const int l1 = ligand_id == -1 ? (int)c->ligs.size() : ligand_id + 1;
   HIP_TRY(launch_exchange(c->d_ligs + l0, l1 - l0, scheme, max_sep, n_sweeps,
-                          scheme == 1 && any_far(c, l0, l1, max_sep), c->seed,
-                          c->stream));
+                          scheme == 1 ? walk_of(c, l0, l1, max_sep) : kWalkNear,
+                          c->seed, c->stream));
   return BPMF_OK;
 }
 

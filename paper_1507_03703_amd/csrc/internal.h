@@ -197,7 +197,7 @@ hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
                             hipStream_t st);
 hipError_t launch_sweep_tail(const LigDev* d_ligs, int n_ligs,
                              int exchange_every, int scheme, int max_sep,
-                             int n_sub, int sample_every, bool far,
+                             int n_sub, int sample_every, int walk,
                              uint64_t seed, hipStream_t st);
 hipError_t launch_sweep_begin(const LigDev* d_ligs, int n_ligs,
                               hipStream_t st);
@@ -206,12 +206,11 @@ hipError_t launch_sweep_finish(const LigDev* d_ligs, int n_ligs,
                                uint64_t seed, hipStream_t st);
 // n_sub exchange sweeps in a row (sweep j draws with replica field j)
 hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
-                           int max_sep, int n_sub, bool far, uint64_t seed,
+                           int max_sep, int n_sub, int walk, uint64_t seed,
                            hipStream_t st);
 // All-separations exchange of K states: up to this separation the residue
 // classes are walked by a wavefront each, eight at a time; past it, where there
-// are many classes of few states, by a lane each, and the exchange of a ladder
-// that goes past it (`far` above) has kernels of its own.  The line is where
+// are many classes of few states, by a lane each.  The line is where
 // both cost the same: a wavefront's walk of a class costs 0.7 us however short
 // the class, all lanes' walks together 0.3 to 1 us by its length.  One sweep
 // over every separation, a wavefront for each class and this way: 64 states
@@ -222,8 +221,18 @@ hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
 __host__ __device__ constexpr int exchange_wave_separations(int K) {
   return K <= 64 ? 8 : K <= 192 ? 16 : 24;
 }
-inline bool exchange_far(int K, int max_sep) {
-  return (max_sep < K - 1 ? max_sep : K - 1) > exchange_wave_separations(K);
+// The kernels of the exchange (`walk` above), by the ladders of a launch: with
+// some ladder past its line, with short ladders only, and the others.  A
+// wavefront doubles its steps along a class three times before it takes them;
+// up to eight positions the steps themselves cost less (up to 5 separations, 25
+// sweeps, doublings always and not there: 4 states 101 and 95 us, 16 states 175
+// and 165 us, 32 states 186 and 184 us), but the test costs the longer ladders
+// more than they gain (64 states 194 and 199 us).
+enum ExchangeWalk : int { kWalkNear = 0, kWalkFar = 1, kWalkShort = 2 };
+inline int exchange_walk(int K, int max_sep) {
+  if ((max_sep < K - 1 ? max_sep : K - 1) > exchange_wave_separations(K))
+    return kWalkFar;
+  return K <= 32 ? kWalkShort : kWalkNear;
 }
 // one ligand's share of an energy-matrix launch: samples xs (n x n_atoms x
 // 3), output u_kn (K x ld); its samples are [first, first + n) of the

@@ -125,6 +125,7 @@ constexpr int kXStates = 256, kXChannels = 5;
 constexpr int kXAhead = 8;      // steps decided ahead of the walk
 constexpr int kXHalf = kXAhead / 2;
 constexpr int kXJump = 3;       // doublings of the walk's step
+constexpr int kXShort = 8;      // positions up to which a walk does without
 constexpr int kXThreads = 512;  // block of the exchange kernels
 struct alignas(16) XStage {
   double cp[kXStates * (1 + kXChannels)];  // components per replica
@@ -179,7 +180,7 @@ constexpr unsigned kXOpen = 1u << 16;  // mark of an open run in the walk
 
 // Step 3 for one class by one wavefront: X.ros[cur] read, the other buffer
 // written.  count: add the accepted swaps of every pair to X.nacc.
-template <int C, bool TABLE>
+template <int C, bool TABLE, int WALK>
 __device__ __forceinline__ void exchange_class(XStage& X, const double* em,
                                                int K, int d, int rho, int cur,
                                                int lb, bool count) {
@@ -206,12 +207,14 @@ __device__ __forceinline__ void exchange_class(XStage& X, const double* em,
     // up to 2^kXJump runs in a row as one: the starts met and what follows
     unsigned mlo = lane < 32 ? 1u << lane : 0u;
     unsigned mhi = lane < 32 ? 0u : 1u << (lane - 32);
+    if (WALK == kWalkNear || T > kXShort) {
 #pragma unroll
-    for (int i = 0; i < kXJump; ++i) {
-      const int src = 4 * (int)(next < lim ? next : (unsigned)lane);
-      mlo |= (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)mlo);
-      mhi |= (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)mhi);
-      next = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)next);
+      for (int i = 0; i < kXJump; ++i) {
+        const int src = 4 * (int)(next < lim ? next : (unsigned)lane);
+        mlo |= (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)mlo);
+        mhi |= (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)mhi);
+        next = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)next);
+      }
     }
     unsigned long long start = 0ull;
     unsigned qr = q - b0;
@@ -329,15 +332,16 @@ __device__ __forceinline__ void exchange_lane(XStage& X, const double* em,
   }
 }
 
-// FAR: some separation is past exchange_wave_separations (a kernel of its own:
+// WALK: the launch's ladders (ExchangeWalk).  kWalkFar has kernels of its own:
 // with both walks in one, the loop's scalars spill and a pass of the nearest
-// separations takes 5 % longer); steps past the end of every class, whose
+// separations takes 5 % longer; steps past the end of every class, whose
 // energies no run asks for, are then left out.
-template <int C, bool TABLE, bool FAR>
+template <int C, bool TABLE, int WALK>
 __device__ __forceinline__ void exchange_all_staged(
     const LigDev& L, uint64_t sweep, int max_sep, int n_sub, uint64_t seed,
     XStage& X, double* em) {
   constexpr int C1 = 1 + C;
+  constexpr bool kFar = WALK == kWalkFar;
   const int K = L.K;
   const int tid = threadIdx.x, nt = blockDim.x;
   const int nw = nt / kWave;
@@ -383,7 +387,7 @@ __device__ __forceinline__ void exchange_all_staged(
   const int dw = exchange_wave_separations(K);
   for (int j = 0; j < n_sub; ++j) {
     for (int d = 1; d <= dmax; ++d) {
-      const bool lanes = FAR && d > dw;
+      const bool lanes = kFar && d > dw;
       const int* ros = X.ros[cur];
       double2* el = X.el[lb];
       // energies of the state's replica at the half's states, the energy at
@@ -400,7 +404,7 @@ __device__ __forceinline__ void exchange_all_staged(
 #pragma unroll
         for (int m = 0; m <= kXHalf; ++m) {
           // steps past every class's end
-          if (FAR && (kXHalf * hu + m) * d >= K) break;
+          if (kFar && (kXHalf * hu + m) * d >= K) break;
           const int s = a + (kXHalf * h + m) * d;
           st[m] = s < K ? s : a;  // past the end: any state (not counted)
           double u[C1];
@@ -420,7 +424,7 @@ __device__ __forceinline__ void exchange_all_staged(
         bool go = true;
 #pragma unroll
         for (int m = 0; m < kXHalf; ++m) {
-          if (FAR && (kXHalf * hu + m + 1) * d >= K) break;
+          if (kFar && (kXHalf * hu + m + 1) * d >= K) break;
           const bool ok = staged_accepts(be[m], be[m + 1], el[st[m]], e[m],
                                          e[m + 1], X.ecur[st[m + 1]]);
           go = (bool)(go & ok & (a + (kXHalf * h + m + 1) * d < K));
@@ -438,7 +442,7 @@ __device__ __forceinline__ void exchange_all_staged(
         draw_pass(jn, dn, lb ^ 1, tid - w0 * kWave, nt - w0 * kWave);
       if (!lanes) {
         for (int rho = wv; rho < d; rho += nw)
-          exchange_class<C, TABLE>(X, em, K, d, rho, cur, lb, d == 1);
+          exchange_class<C, TABLE, WALK>(X, em, K, d, rho, cur, lb, d == 1);
       } else if (tid < d) {
         exchange_lane<C, TABLE>(X, em, K, d, tid, cur, lb);
       }
@@ -463,7 +467,7 @@ __device__ __forceinline__ void exchange_all_staged(
 // exchange sweeps in a row, sweep j drawing its uniforms with replica field j
 // Inlined into its kernels, with everything below it: in a called function
 // the staged data's pointers are generic and every access a flat one.
-template <bool FAR>
+template <int WALK>
 __device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
                                                int scheme, int max_sep,
                                                int n_sub, uint64_t seed) {
@@ -480,17 +484,17 @@ __device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
         attempt_pair(L, a, a + 1, 1, sweep, j, seed);
     }
   } else if (K <= kXTable && L.C == 3) {
-    exchange_all_staged<3, true, FAR>(L, sweep, max_sep, n_sub, seed, X,
-                                      em);
+    exchange_all_staged<3, true, WALK>(L, sweep, max_sep, n_sub, seed, X,
+                                       em);
   } else if (K <= kXTable && L.C == 5) {
-    exchange_all_staged<5, true, FAR>(L, sweep, max_sep, n_sub, seed, X,
-                                      em);
+    exchange_all_staged<5, true, WALK>(L, sweep, max_sep, n_sub, seed, X,
+                                       em);
   } else if (K <= kXStates && L.C == 3) {
-    exchange_all_staged<3, false, FAR>(L, sweep, max_sep, n_sub, seed, X,
-                                      em);
+    exchange_all_staged<3, false, WALK>(L, sweep, max_sep, n_sub, seed, X,
+                                       em);
   } else if (K <= kXStates && L.C == 5) {
-    exchange_all_staged<5, false, FAR>(L, sweep, max_sep, n_sub, seed, X,
-                                      em);
+    exchange_all_staged<5, false, WALK>(L, sweep, max_sep, n_sub, seed, X,
+                                       em);
   } else if (threadIdx.x == 0) {
     const int dmax = max_sep < K - 1 ? max_sep : K - 1;
     for (int j = 0; j < n_sub; ++j)
@@ -506,13 +510,13 @@ __device__ __forceinline__ void exchange_block(const LigDev& L, uint64_t sweep,
 
 // Tail of one ligand's sweep, run by one whole block: exchange (if due),
 // record one sample per state (if due), counter += 1.
-template <bool FAR>
+template <int WALK>
 __device__ __forceinline__ void sweep_tail(const LigDev& L, int exchange_every,
                                            int scheme, int max_sep, int n_sub,
                                            int sample_every, uint64_t seed) {
   const unsigned long long s = *L.counter;
   if (exchange_every > 0 && s % (unsigned long long)exchange_every == 0ull)
-    exchange_block<FAR>(L, s, scheme, max_sep, n_sub, seed);
+    exchange_block<WALK>(L, s, scheme, max_sep, n_sub, seed);
   __syncthreads();
   const unsigned long long rec = *L.n_rec;
   const bool record = sample_every > 0 &&
@@ -539,11 +543,11 @@ __device__ __forceinline__ void sweep_tail(const LigDev& L, int exchange_every,
 }
 
 // One block per ligand: the tail as a kernel of its own.
-template <bool FAR>
+template <int WALK>
 __global__ __launch_bounds__(kXThreads) void k_sweep_tail(
     const LigDev* __restrict__ ligs, int exchange_every, int scheme,
     int max_sep, int n_sub, int sample_every, uint64_t seed) {
-  sweep_tail<FAR>(ligs[blockIdx.x], exchange_every, scheme, max_sep, n_sub,
+  sweep_tail<WALK>(ligs[blockIdx.x], exchange_every, scheme, max_sep, n_sub,
              sample_every, seed);
 }
 
@@ -869,12 +873,12 @@ __global__ __launch_bounds__(W * kWave) void k_hmc_sweep(
   }
 }
 
-template <bool FAR>
+template <int WALK>
 __global__ __launch_bounds__(kXThreads) void k_exchange(
     const LigDev* __restrict__ ligs, int scheme, int max_sep, int n_sub,
     uint64_t seed) {
   const LigDev& L = ligs[blockIdx.x];
-  exchange_block<FAR>(L, *L.counter, scheme, max_sep, n_sub, seed);
+  exchange_block<WALK>(L, *L.counter, scheme, max_sep, n_sub, seed);
 }
 
 // ----------------------------------------------------------------------------
@@ -1495,10 +1499,12 @@ hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
 
 hipError_t launch_sweep_tail(const LigDev* d_ligs, int n_ligs,
                              int exchange_every, int scheme, int max_sep,
-                             int n_sub, int sample_every, bool far,
+                             int n_sub, int sample_every, int walk,
                              uint64_t seed, hipStream_t st) {
   if (n_ligs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(far ? k_sweep_tail<true> : k_sweep_tail<false>,
+  hipLaunchKernelGGL(walk == kWalkFar     ? k_sweep_tail<kWalkFar>
+                     : walk == kWalkShort ? k_sweep_tail<kWalkShort>
+                                          : k_sweep_tail<kWalkNear>,
                      dim3(n_ligs), dim3(kXThreads), 0, st, d_ligs,
                      exchange_every, scheme, max_sep, n_sub, sample_every,
                      seed);
@@ -1522,12 +1528,14 @@ hipError_t launch_sweep_finish(const LigDev* d_ligs, int n_ligs,
 }
 
 hipError_t launch_exchange(const LigDev* d_lig, int n_ligs, int scheme,
-                           int max_sep, int n_sub, bool far, uint64_t seed,
+                           int max_sep, int n_sub, int walk, uint64_t seed,
                            hipStream_t st) {
   if (n_ligs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(far ? k_exchange<true> : k_exchange<false>, dim3(n_ligs),
-                     dim3(kXThreads), 0, st, d_lig, scheme, max_sep, n_sub,
-                     seed);
+  hipLaunchKernelGGL(walk == kWalkFar     ? k_exchange<kWalkFar>
+                     : walk == kWalkShort ? k_exchange<kWalkShort>
+                                          : k_exchange<kWalkNear>,
+                     dim3(n_ligs), dim3(kXThreads), 0, st, d_lig, scheme,
+                     max_sep, n_sub, seed);
   return hipGetLastError();
 }
 

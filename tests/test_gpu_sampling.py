@@ -284,6 +284,43 @@ def test_exchange_far_separations(K, C, max_sep, scale):
     ctx.close()
 
 
+@pytest.mark.parametrize("Ks,C,max_sep", [
+    ((4,), 5, 3), ((8,), 3, 7), ((9,), 5, 8), ((17,), 3, 5), ((32,), 5, 5),
+    ((33,), 3, 5), ((8, 32), 3, 5), ((4, 33), 5, 5), ((8, 40), 3, 9)])
+@pytest.mark.parametrize("scale", [0.02, 0.6])
+def test_exchange_short_ladders(Ks, C, max_sep, scale):
+    """All-separation sweeps of ladders around 32 states, whose classes of up
+    to eight positions are walked without doublings, and of launches with
+    ladders on either side of that and of the far separations' line.  Labels
+    and counts equal the oracle's."""
+    print_case("exchange short", Ks, C, max_sep, scale)
+    made = [_exchange_ligand(K, C) for K in Ks]
+    g, ligs = made[0][0], [lig for _, lig in made]
+    ctx, ids = make_context(g, ligs, seed=33)
+    want = []
+    for lid, lig, K in zip(ids, ligs, Ks):
+        rng = np.random.default_rng([4, K, C, int(100 * scale)])
+        comps = rng.normal(scale=scale, size=(K, 1 + C))
+        sor = rng.permutation(K).astype(np.int32)
+        ctx.set_replicas(lid, lig.x0, sor, comps, 8)
+        s = oracle.Sampler(oracle.OGrid(g), oracle.OLigand(lig), seed=33,
+                           lig_id=lid, x0=lig.x0)
+        s.comps = np.ascontiguousarray(comps)
+        s.state = sor.copy()
+        s.rep_of_state = np.ascontiguousarray(np.argsort(sor).astype(np.int32))
+        s.sweep_count = 8
+        s.exchange(scheme=1, max_sep=max_sep, n_sweeps=25)
+        want.append(s)
+    ctx.exchange(-1, scheme=1, max_sep=max_sep, n_sweeps=25)
+    for lid, s in zip(ids, want):
+        assert np.array_equal(ctx.get_replicas(lid)["state_of_replica"],
+                              s.state)
+        stats = ctx.get_stats(lid)
+        assert np.array_equal(stats["ex_try"], s.ex_try)
+        assert np.array_equal(stats["ex_acc"], s.ex_acc)
+    ctx.close()
+
+
 def test_exchange_far_separations_cost_no_more_than_near_ones():
     """A separation with many short classes is not dearer than one with few
     long ones (a wavefront for each of them, eight at a time, made it five
