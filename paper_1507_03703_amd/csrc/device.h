@@ -683,8 +683,12 @@ __device__ __forceinline__ void block_sync() {
 // what overlaps chains must not add instructions: 48 atoms on 8 wavefronts
 // have 6 partners a thread, and 20 sweeps of 20 steps take 3.21 ms with 3 at
 // a time, 3.36 with 2 or with 4 (two idle of 8), 3.40 with 6, 4.31 with 8;
-// one at a time through branches 3.63 ms.
-constexpr int kPairAhead = 3;
+// one at a time through branches 3.63 ms.  A ligand whose threads have no more
+// than 2 partners takes 2 at a time, in sweep kernels of its own (chosen by a
+// branch, the longer slices lose 2 %): 8 atoms, 64 replicas, 20 sweeps of 20
+// steps on 4 and 8 wavefronts 2.05 and 1.82 ms, 2.52 and 2.08 ms with 3, 2.37
+// and 1.88 ms one at a time through branches.
+constexpr int kPairAhead = 3, kPairShort = 2;
 
 // a pair's force factor; its two terms are rounded before their sum
 __device__ __forceinline__ float pair_force(float flj, float fcl, float c14,
@@ -709,7 +713,7 @@ __device__ __forceinline__ float pair_force(float flj, float fcl, float c14,
 // -b_i v_i - sum_j b_j dH(r_ij; a_j, s_i) (x_i - x_j) / r_ij, with
 // b = dE/dR dR/dI.  e: the owner's share of the energy; pf: the force on
 // its atom (FORCES); both 0 on other threads.
-template <bool FORCES>
+template <bool FORCES, int AHEAD>
 __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
                                            int n, int tid, int nthreads,
                                            float& e, float (&pf)[3]) {
@@ -746,9 +750,9 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
     float I = 0.f, e_lj = 0.f, e_c = 0.f, fx = 0.f, fy = 0.f, fz = 0.f;
     float vx = 0.f, vy = 0.f, vz = 0.f;
     const float ra = __builtin_amdgcn_rcpf(qi1.x);
-    for (int jb = j0; jb < j1; jb += kPairAhead)
+    for (int jb = j0; jb < j1; jb += AHEAD)
 #pragma unroll
-    for (int u = 0; u < kPairAhead; ++u) {
+    for (int u = 0; u < AHEAD; ++u) {
       const int j = jb + u < j1 ? jb + u : j1 - 1;
       const bool self = jb + u >= j1 || j == i;  // or past the slice
       const float4 xj = sh.pos[j], pj = sh.pp0[j];
@@ -825,9 +829,9 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
     const float qi = pi.x, Rii = sh.pR[i];
     float e_gb = 0.f, dEdR = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
     const float kqi = P.kgb * qi;
-    for (int jb = j0; jb < j1; jb += kPairAhead)
+    for (int jb = j0; jb < j1; jb += AHEAD)
 #pragma unroll
-    for (int u = 0; u < kPairAhead; ++u) {
+    for (int u = 0; u < AHEAD; ++u) {
       const int j = jb + u < j1 ? jb + u : j1 - 1;
       const float4 xj = sh.pos[j];
       const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
@@ -884,9 +888,9 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
     // the atom's own from v_i
     if (act) {
       float gx = 0.f, gy = 0.f, gz = 0.f;
-      for (int jb = j0; jb < j1; jb += kPairAhead)
+      for (int jb = j0; jb < j1; jb += AHEAD)
 #pragma unroll
-      for (int u = 0; u < kPairAhead; ++u) {
+      for (int u = 0; u < AHEAD; ++u) {
         const int j = jb + u < j1 ? jb + u : j1 - 1;
         const float4 xj = sh.pos[j];
         const float2 pj1 = sh.pp1[j];
@@ -934,11 +938,11 @@ __device__ __forceinline__ void pair_stage(const Shared& sh, const PairDev& P,
 // BONDED false: the grid terms and the restraint only (terms[0..2] = 0; no
 // topology needs to be staged), for rigid moves, which leave the bonded
 // energy unchanged.
-// PAIRS: the ligand's pair terms join the energy when L.pairs_on (their
-// energy is summed with the bonded terms, in terms[0]; their force is part
+// PAIRS (partners at once, or 0): the ligand's pair terms join the energy when
+// L.pairs_on (their energy is summed with the bonded terms, in terms[0]; their force is part
 // of the state-independent force).
 template <int C, int W, bool FORCES, bool ENERGY, bool LEAN = false,
-          bool BONDED = true, bool PAIRS = false, bool TERMS0 = false>
+          bool BONDED = true, int PAIRS = 0, bool TERMS0 = false>
 __device__ __forceinline__ void eval_block(const GridDev& g, const LigDev& L,
                                            const float* w, const float (&x)[3],
                                            float m, const float (&sc)[C],
@@ -1036,8 +1040,9 @@ __device__ __forceinline__ void eval_block(const GridDev& g, const LigDev& L,
   }
   // intramolecular nonbonded and implicit-solvent terms
   float epair = 0.f, fpair[3] = {0.f, 0.f, 0.f};
-  const bool pairs = PAIRS && L.pairs_on;
-  if (pairs) pair_stage<FORCES>(sh, L.pair, n, tid, W * kWave, epair, fpair);
+  const bool pairs = PAIRS > 0 && L.pairs_on;
+  if (pairs)
+    pair_stage<FORCES, PAIRS>(sh, L.pair, n, tid, W * kWave, epair, fpair);
   // centre of mass offset from the site (an atom wave's own total, which
   // wave 0 publishes for the others)
   float cx, cy, cz;

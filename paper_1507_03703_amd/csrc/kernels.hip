@@ -573,9 +573,9 @@ __global__ __launch_bounds__(256) void k_sweep_finish(
 // ONE: the launch covers the replicas of a single ligand, whose table entry
 // comes in the kernel arguments (block b = replica b) instead of through the
 // task list.
-// PAIRS: ligands whose pair terms are in the energy (L.pairs_on) evaluate
-// them too.
-template <int C, int W, bool ONE, bool PAIRS>
+// PAIRS (partners at once, or 0): ligands whose pair terms are in the energy
+// (L.pairs_on) evaluate them too.
+template <int C, int W, bool ONE, int PAIRS>
 __global__ __launch_bounds__(W * kWave) void k_hmc_sweep(
     GridDev g, const LigDev* __restrict__ ligs, const int2* __restrict__ tasks,
     LigDev one, int nleap, uint64_t seed, TailArgs tail) {
@@ -979,7 +979,7 @@ __global__ __launch_bounds__(W * kWave) void k_energy_matrix(
             xn[d] = owner ? xb[(size_t)(q + 1 - J.first) * n * 3 + d] : 0.f;
         }
         double t[6 + C];
-        eval_block<C, W, false, true, true, true, PAIRS>(
+        eval_block<C, W, false, true, true, true, PAIRS ? kPairAhead : 0>(
             g, L, w0, x, m, sc, f, t, 0.f, 0.f, sh, tid);
         const double U0 = t[0] + t[1] + t[2] + t[3];
         double* cs = col + (q - s) * K;
@@ -1349,8 +1349,8 @@ __global__ __launch_bounds__(W * kWave) void k_recompute(
   for (int d = 0; d < 3; ++d)
     x[d] = owner ? L.x[((size_t)r * n + tid) * 3 + d] : 0.f;
   double t[6 + C];
-  eval_block<C, W, false, true, false, true, PAIRS>(g, L, w0, x, m, sc, f, t,
-                                                    0.f, 0.f, sh, tid);
+  eval_block<C, W, false, true, false, true, PAIRS ? kPairAhead : 0>(
+      g, L, w0, x, m, sc, f, t, 0.f, 0.f, sh, tid);
   if (tid == 0) {
     double* cp = L.comps + (size_t)r * (1 + C);
     cp[0] = t[0] + t[1] + t[2] + t[3];
@@ -1484,14 +1484,17 @@ hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
                        dim3(W * kWave), lds_bytes, st, g, d_ligs, d_tasks,  \
                        arg, nleap, seed, tail);                             \
   }))
-  if (one && pairs) {
-    BPMF_SWEEP(true, true);
+  // (one wavefront holds slices of two partners for no ligand of use)
+  if (one && pairs && one->n <= kPairShort * pair_slices(one->n, waves)) {
+    BPMF_SWEEP(true, (W > 1 ? kPairShort : kPairAhead));
+  } else if (one && pairs) {
+    BPMF_SWEEP(true, kPairAhead);
   } else if (one) {
-    BPMF_SWEEP(true, false);
+    BPMF_SWEEP(true, 0);
   } else if (pairs) {
-    BPMF_SWEEP(false, true);
+    BPMF_SWEEP(false, kPairAhead);
   } else {
-    BPMF_SWEEP(false, false);
+    BPMF_SWEEP(false, 0);
   }
 #undef BPMF_SWEEP
   return hipGetLastError();
