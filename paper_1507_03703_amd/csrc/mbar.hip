@@ -732,7 +732,10 @@ __global__ __launch_bounds__(kSelfT) void k_self_consistent(
 // 256 blocks, since a block's partial sums are as large as its share of a
 // small problem's u_kn (32 problems of 32 x 6400: 1, 2, 3, 4, 6 and 8 chunks
 // give 21.6, 21.0, 21.5, 23.3, 25.1 and 25.5 us).  Many: a block a CU, each
-// iteration 64 samples.
+// iteration 64 samples.  With these, calls of 1 to 32 problems of 2 to 128
+// states and 1 to 800 samples a state take 1/2.3 to 1/23 of the time of the
+// separate passes with a host decision each, the fewest where 32 problems of 17
+// states have 800.
 int mbar_blocks(int K, int64_t N) {
   const int64_t per = mbar_tiles(K) <= kMbarNarrow ? 128 : 64;
   return (int)std::min<int64_t>(256, (N + per - 1) / per);

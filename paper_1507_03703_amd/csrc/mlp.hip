@@ -437,8 +437,10 @@ __global__ __launch_bounds__(kFWaves * 64) void k_train_rows(TrainArgs a) {
       sw[d] = kSw0 + (kSw1 - kSw0) * sigm(o[10 + d]);
     }
     // One difference of the 24 is a single rounding of t - pi tanh, the others
-    // of t - fl(pi tanh): a step's bits decide those of the steps after it
-    // (bf16 roundings flip), so the places of the roundings are fixed here.
+    // of t - fl(pi tanh).  Nothing in the mathematics asks for it: an earlier
+    // compilation fused that one product.  It is kept because a step's bits
+    // decide those of the steps after it (bf16 roundings flip): with one form
+    // for all, 20 steps end in other weights, as far from the 64-bit ones.
     const float last = fmaf(-(float)M_PI, th[2], pose[5]);
     float lg = lw - 3.0f * logf(2.0f * (float)M_PI);
 #pragma unroll

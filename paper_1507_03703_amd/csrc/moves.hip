@@ -456,7 +456,8 @@ hipError_t launch_place_poses(const LigDev* lig, int n, const float* confs,
   // wait: 33 us with 64 to a workgroup, 23 us with 8)
   const int per = (int)std::min<int64_t>(
       kPlacePoses, std::max<int64_t>(8, (count + 1023) / 1024 * 4));
-  const int64_t most = ((1ll << 24) - 1) * per;  // a launch's
+  // a launch's (only ligands of up to three atoms need more than one)
+  const int64_t most = ((1ll << 24) - 1) * per;
   for (int64_t done = 0; done < count; done += most) {
     const int64_t now = std::min(count - done, most);
     hipLaunchKernelGGL(k_place_poses, dim3((unsigned)((now + per - 1) / per)),

@@ -33,12 +33,16 @@ constexpr float kObcA = 1.0f, kObcB = 0.8f, kObcC = 4.85f;
 // du/u = -u and dl/l = -+l are used as such.  Without branches: every lane of
 // a wavefront has pairs on either side of each condition, so branches would
 // be walked both ways, and partners' chains would not overlap.  Roundings are
-// placed by hand, so that every caller gets the same bits; OWN: s is the
-// atom's own for all partners (s^2 rounded by itself).
+// placed by hand, so that a use's bits do not depend on what the compiler makes
+// of the code around it.  OWN, for the uses in which s is the atom's own for all
+// partners: s^2 is rounded and r^2 is not, elsewhere the other way round; a
+// trajectory's decisions follow from these bits, so both uses keep theirs.
 //
-// The logarithm is __logf for a normal argument (u x is at least a / (r + s)):
-// its scaling of subnormal arguments and its care of infinities left out, the
-// same value.
+// The logarithm is for normal arguments (u x is at least a / (r + s)): log2, by
+// the hardware, times ln 2 in two parts, the rounding error of the leading
+// product recovered by a fused multiply-add (the exact product of Dekker, 1971).
+// That is what __logf gives there, without its scaling of subnormal arguments
+// and its care of infinities.
 __device__ __forceinline__ float hct_log(float v) {
   constexpr float kLn2 = 0x1.62e42ep-1f, kLn2Low = 0x1.efa39ep-25f;
   const float y = __builtin_amdgcn_logf(v);  // log2
