@@ -116,7 +116,7 @@ struct bpmf_ctx {
   int class_n[kWaveClasses] = {0, 0, 0, 0};
   int class_lds[kWaveClasses] = {0, 0, 0, 0};
   int class_single[kWaveClasses] = {-1, -1, -1, -1};  // sole ligand or -1
-  bool class_pairs[kWaveClasses] = {false, false, false, false};
+  int class_pairs[kWaveClasses] = {0, 0, 0, 0};  // pair partners at once
   int waves_override = 0;  // 0 = automatic choice
   int task_order = 1;      // 0 = ligand by ligand, 1 = heaviest first
   int n_cu = 1;  // compute units of the device
@@ -284,7 +284,7 @@ int rebuild_tables(bpmf_ctx* c) {
   std::vector<LigDev> table(nl);
   std::vector<int2> cls[bpmf_ctx::kWaveClasses];
   int lds[bpmf_ctx::kWaveClasses] = {0, 0, 0, 0};
-  bool pairs[bpmf_ctx::kWaveClasses] = {false, false, false, false};
+  int pairs[bpmf_ctx::kWaveClasses] = {0, 0, 0, 0};
   int total = 0;
   for (int l = 0; l < nl; ++l) total += c->ligs[l].dev.K;
   for (int l = 0; l < nl; ++l) {
@@ -294,7 +294,8 @@ int rebuild_tables(bpmf_ctx* c) {
     const int q = wave_class(h.sweep_waves);
     for (int r = 0; r < h.dev.K; ++r) cls[q].push_back(make_int2(l, r));
     lds[q] = std::max(lds[q], lds_of(h, h.sweep_waves, true));
-    pairs[q] = pairs[q] || h.dev.pairs_on;
+    if (h.dev.pairs_on)
+      pairs[q] = std::max(pairs[q], pair_at_once(h.dev.n, h.sweep_waves));
   }
   if (c->task_order == 1) {
     // the replicas of the ligands with the most work per sweep first (a
@@ -1022,7 +1023,9 @@ static int hmc_sweep_impl(bpmf_ctx* c, const bpmf_sweep_args* a, int only) {
       HIP_TRY(launch_hmc_sweep(c->grid, c->d_ligs, nullptr, h.dev.K,
                                h.sweep_waves, lds_of(h, h.sweep_waves, true),
                                a->n_leapfrog, c->seed, tail, &h.dev,
-                               h.dev.pairs_on != 0, st));
+                               h.dev.pairs_on
+                                   ? pair_at_once(h.dev.n, h.sweep_waves) : 0,
+                               st));
     } else {
       // classes hold different ligands: the first runs on `st`, each other
       // one on a stream of its own forked from `st` and joined back after

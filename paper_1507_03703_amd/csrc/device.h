@@ -678,20 +678,6 @@ __device__ __forceinline__ void block_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Partners whose chains of a pass run side by side (pair_stage).  A replica's
-// wavefronts share one CU and issue for some three quarters of the time, so
-// what overlaps chains must not add instructions: 48 atoms on 8 wavefronts
-// have 6 partners a thread, and 20 sweeps of 20 steps take 3.21 ms with 3 at
-// a time, 3.36 with 2 or with 4 (two idle of 8), 3.40 with 6, 4.31 with 8;
-// one at a time through branches 3.63 ms (12 to 100 atoms on 1 to 8 wavefronts:
-// 1 to 42 % faster so, least where 32 atoms on 8 leave two of six idle).  A
-// ligand whose threads have no more
-// than 2 partners takes 2 at a time, in sweep kernels of its own (chosen by a
-// branch, the longer slices lose 2 %): 8 atoms, 64 replicas, 20 sweeps of 20
-// steps on 4 and 8 wavefronts 2.05 and 1.82 ms, 2.52 and 2.08 ms with 3, 2.37
-// and 1.88 ms one at a time through branches.
-constexpr int kPairAhead = 3, kPairShort = 2;
-
 // a pair's force factor; its two terms are rounded before their sum
 __device__ __forceinline__ float pair_force(float flj, float fcl, float c14,
                                             bool off) {

@@ -189,11 +189,12 @@ struct TailArgs {
 };
 // one: the host copy of the table entry when the launch covers a single
 // ligand (its replicas 0..n_tasks-1 in order), else null
-// pairs: some ligand of the launch has its pair terms in the energy
+// pairs: partners at once (the most pair_at_once of the launch's ligands with
+// their pair terms in the energy; 0: none has)
 hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
                             const int2* d_tasks, int n_tasks, int waves,
                             int lds_bytes, int nleap, uint64_t seed,
-                            TailArgs tail, const LigDev* one, bool pairs,
+                            TailArgs tail, const LigDev* one, int pairs,
                             hipStream_t st);
 hipError_t launch_sweep_tail(const LigDev* d_ligs, int n_ligs,
                              int exchange_every, int scheme, int max_sep,

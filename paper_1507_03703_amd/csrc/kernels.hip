@@ -1473,7 +1473,7 @@ int grid_blocks(int64_t work, int per_block, int cap) {
 hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
                             const int2* d_tasks, int n_tasks, int waves,
                             int lds_bytes, int nleap, uint64_t seed,
-                            TailArgs tail, const LigDev* one, bool pairs,
+                            TailArgs tail, const LigDev* one, int pairs,
                             hipStream_t st) {
   if (n_tasks <= 0) return hipSuccess;
   const LigDev none{};
@@ -1484,13 +1484,14 @@ hipError_t launch_hmc_sweep(const GridDev& g, const LigDev* d_ligs,
                        dim3(W * kWave), lds_bytes, st, g, d_ligs, d_tasks,  \
                        arg, nleap, seed, tail);                             \
   }))
-  // (one wavefront holds slices of two partners for no ligand of use)
-  if (one && pairs && one->n <= kPairShort * pair_slices(one->n, waves)) {
+  if (one && pairs == kPairShort) {  // on two wavefronts or more
     BPMF_SWEEP(true, (W > 1 ? kPairShort : kPairAhead));
   } else if (one && pairs) {
     BPMF_SWEEP(true, kPairAhead);
   } else if (one) {
     BPMF_SWEEP(true, 0);
+  } else if (pairs == kPairShort) {
+    BPMF_SWEEP(false, (W > 1 ? kPairShort : kPairAhead));
   } else if (pairs) {
     BPMF_SWEEP(false, kPairAhead);
   } else {

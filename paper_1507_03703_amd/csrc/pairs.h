@@ -25,6 +25,23 @@ __host__ __device__ inline int pair_lds_bytes(int n, int waves) {
   return 64 * n + 16 + 36 * n * pair_slices(n, waves);
 }
 
+// Partners whose chains of a pass run side by side (pair_stage).  A replica's
+// wavefronts share one CU and issue for some three quarters of the time, so
+// what overlaps chains must not add instructions: 48 atoms on 8 wavefronts
+// have 6 partners a thread, and 20 sweeps of 20 steps take 3.21 ms with 3 at
+// a time, 3.36 with 2 or with 4 (two idle of 8), 3.40 with 6, 4.31 with 8;
+// one at a time through branches 3.63 ms (12 to 100 atoms on 1 to 8 wavefronts:
+// 1 to 42 % faster so, least where 32 atoms on 8 leave two of six idle).
+// Ligands whose threads have no more than 2 partners take 2 at a time, in sweep
+// kernels of their own (chosen by a branch, the longer slices lose 2 %): 8
+// atoms, 64 replicas, 20 sweeps of 20 steps on 4 and 8 wavefronts 2.05 and 1.82
+// ms, 2.52 and 2.08 ms with 3, 2.37 and 1.88 ms one at a time through branches.
+constexpr int kPairAhead = 3, kPairShort = 2;
+inline int pair_at_once(int n, int waves) {
+  return waves > 1 && n <= kPairShort * pair_slices(n, waves) ? kPairShort
+                                                              : kPairAhead;
+}
+
 constexpr float kObcA = 1.0f, kObcB = 0.8f, kObcC = 4.85f;
 
 // Descreening integral H(r; a, s) of a ball of radius s at distance r outside

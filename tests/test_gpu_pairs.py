@@ -281,25 +281,26 @@ def test_pair_slices_of_uneven_length(n, waves):
                                      (15, 8), (16, 8), (17, 8)])
 def test_pair_partners_two_at_a_time(n, waves):
     """Ligands around two partners a thread, which take them two at a time when
-    they are swept alone: the replicas are those of the same ligand swept in a
-    batch, three at a time, bit for bit."""
+    every ligand of the launch does: the replicas are those of the same ligand
+    swept beside a larger one, three at a time, bit for bit."""
     print_case("pair partners", n, waves)
     g, lig, p = _full_pathway_system(n, K=4)
-    other = synth.make_ligand(np.random.default_rng(3), 5, 2)
+    _, large, pl = _full_pathway_system(24, K=2)
 
-    def swept(alone):
-        ctx, ids = make_context(g, [lig] if alone else [lig, other], seed=19)
+    def swept(*others):
+        ctx, ids = make_context(g, [lig] + [o for o, _ in others], seed=19)
         ctx.set_waves(waves)
-        for lid in ids[:1]:
-            ctx.pair_setup(lid, p)
+        for lid, q in zip(ids, [p] + [q for _, q in others]):
+            ctx.pair_setup(lid, q)
             ctx.pair_sample(lid, True)
         ctx.hmc_sweep(6, 8)
         st = ctx.get_replicas(ids[0])
         ctx.close()
         return st
-    a, b = swept(True), swept(False)
-    for k in ("x", "state_of_replica", "comps"):
-        assert np.array_equal(a[k], b[k]), k
+    a = swept((large, pl))
+    for b in (swept(), swept((lig, p))):
+        for k in ("x", "state_of_replica", "comps"):
+            assert np.array_equal(a[k], b[k]), k
 
 
 def test_pair_sample_needs_parameters():
