@@ -57,19 +57,19 @@ GRID_BYTES_PER_EVAL = 96  # 8 corners x 3 channels x 4 B
 # kernel and workload: one sweep launch (at the given wavefronts per
 # replica), one harness launch, one energy-matrix call (its launches
 # summed); valid only while the kernel sources hash to TRAFFIC_SOURCES
-TRAFFIC_SOURCES = "a4b8a4de5a8f1693"
+TRAFFIC_SOURCES = "b84b011f6ef68f95"
 TRAFFIC_SCALE = {"fetch": 2.0, "write": 1.0}
 TRAFFIC = {
     ("k_hmc_sweep", "c5_large_batched"):
-        {"waves": 4, "fetch_kib": 9074.867, "write_kib": 4431.230},
+        {"waves": 4, "fetch_kib": 9086.145, "write_kib": 4431.270},
     ("k_hmc_sweep", "c2_plain_production"):
-        {"waves": None, "fetch_kib": 756.941, "write_kib": 198.215},
+        {"waves": None, "fetch_kib": 756.938, "write_kib": 198.215},
     ("k_hmc_sweep", "c3_batched_uneven"):
-        {"waves": 2, "fetch_kib": 37089.032, "write_kib": 23616.901},
+        {"waves": 2, "fetch_kib": 37115.837, "write_kib": 23616.788},
     ("k_grid_eval", "c3_batched_uneven"):
-        {"waves": None, "fetch_kib": 3379883.500, "write_kib": 3383700.000},
+        {"waves": None, "fetch_kib": 3380010.031, "write_kib": 3383700.000},
     ("k_energy_matrix", "c3_batched_uneven"):
-        {"waves": None, "fetch_kib": 1271147.578, "write_kib": 587894.492},
+        {"waves": None, "fetch_kib": 1271220.313, "write_kib": 587743.586},
 }
 KERNEL_SOURCES = ("device.h", "kernels.hip", "internal.h")
 
